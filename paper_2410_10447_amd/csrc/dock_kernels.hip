@@ -28,6 +28,11 @@
 #include "dock_blob.h"
 #include "dock_launch.h"
 
+// No fused operation but those written out (fmaf), so that every kernel that
+// evaluates an individual rounds alike whatever else the compiler finds to
+// share there: searches amplify a last-bit difference within a few steps.
+#pragma clang fp contract(off)
+
 namespace {
 
 using dockblob::Header;
@@ -118,18 +123,41 @@ __device__ __forceinline__ const __attribute__((address_space(1))) T* gmem(const
     return (const __attribute__((address_space(1))) T*)(p);
 }
 
+// Broadcast of lane `c` of each 16-lane row to that row.
+template <int C>
+__device__ __forceinline__ float row_lane(float v) { return dpp<0x150 + C>(v); }
+
+// The DPP steps of the sums and scans below, one instruction per step. They
+// are written out because the compiler does not fold a masked row broadcast
+// into the addition (a zero, a move and an addition instead of one v_add).
+// Lanes whose source lies outside their row add 0; rows a broadcast masks off
+// keep their value. A DPP operand must have been written at least two
+// instructions before: N independent values are stepped side by side, with
+// waits only where fewer than three are.
+#define DPP_STEP(r, how) "v_add_f32_dpp " r ", " r ", " r " " how "\n\t"
+#define DPP_ROW "row_mask:0xf bank_mask:0xf bound_ctrl:1"
+#define DPP_STEP1(how) DPP_STEP("%0", how) "s_nop 1\n\t"
+#define DPP_STEP4(how) DPP_STEP("%0", how) DPP_STEP("%1", how) DPP_STEP("%2", how) DPP_STEP("%3", how)
+#define DPP_STEP6(how) DPP_STEP4(how) DPP_STEP("%4", how) DPP_STEP("%5", how)
+#define DPP_ROW_SUM(STEP) \
+    STEP("quad_perm:[1,0,3,2] " DPP_ROW) STEP("quad_perm:[2,3,0,1] " DPP_ROW) \
+    STEP("row_half_mirror " DPP_ROW) STEP("row_mirror " DPP_ROW)
+#define DPP_ROW_SCAN(STEP) \
+    STEP("row_shr:1 " DPP_ROW) STEP("row_shr:2 " DPP_ROW) STEP("row_shr:4 " DPP_ROW) STEP("row_shr:8 " DPP_ROW)
+#define DPP_HALF(STEP) STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
+#define DPP_WAVE(STEP) DPP_HALF(STEP) STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
+
 // Sum over the wave, every lane receives the same value. Butterfly inside
 // each 16-lane row with DPP (quad swaps, half-row and row mirrors), then the
 // row sums S0..S3 are combined by row broadcasts as (S3 + S2) + (S1 + S0)
 // in the last lane, which is read as a scalar.
 __device__ __forceinline__ float wave_sum(float v) {
-    v += dpp<0xB1>(v);         // quad_perm [1,0,3,2]
-    v += dpp<0x4E>(v);         // quad_perm [2,3,0,1]
-    v += dpp<0x141>(v);        // row_half_mirror
-    v += dpp<0x140>(v);        // row_mirror
-    v += dpp<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP1) DPP_WAVE(DPP_STEP1) : "+v"(v));
     return readlane(v, 63);
+}
+__device__ __forceinline__ float4 wave_sum4(float4 v) {
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) DPP_WAVE(DPP_STEP4) : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    return make_float4(readlane(v.x, 63), readlane(v.y, 63), readlane(v.z, 63), readlane(v.w, 63));
 }
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -140,15 +168,10 @@ __device__ __forceinline__ float wave_max(float v) {
     return fmaxf(fmaxf(readlane(v, 0), readlane(v, 16)), fmaxf(readlane(v, 32), readlane(v, 48)));
 }
 
-// Inclusive prefix sum over the 64 lanes.
-__device__ __forceinline__ float wave_scan(float v) {
-    v += dpp<0x111>(v);          // row_shr:1
-    v += dpp<0x112>(v);          // row_shr:2
-    v += dpp<0x114>(v);          // row_shr:4
-    v += dpp<0x118>(v);          // row_shr:8
-    v += dpp<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
-    v += dpp<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3
-    return v;
+// Inclusive prefix sums of six values over the 64 lanes.
+__device__ __forceinline__ void wave_scan6(float v[6]) {
+    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_WAVE(DPP_STEP6)
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
 }
 
 // ---------------------------------------------------------------------------
@@ -158,7 +181,7 @@ __device__ __forceinline__ float wave_scan(float v) {
 // R0: plain wavefront shuffle (the Sec. 3 baseline without its atomics and
 // barriers: one wave needs neither).
 __device__ __forceinline__ float4 sum4_shuffle(float4 v) {
-    return make_float4(wave_sum(v.x), wave_sum(v.y), wave_sum(v.z), wave_sum(v.w));
+    return wave_sum4(v);
 }
 
 // Tail shared by the MFMA variants. The 16x16 result holds, in column n,
@@ -263,6 +286,16 @@ __device__ __forceinline__ float4 sum4(float4 v) {
     else return sum4_mfma_bf16<3>(v);
 }
 
+// The sum of one value, as the first component of sum4<VAR>.
+template <int VAR>
+__device__ __forceinline__ float sum1(float v) {
+    if constexpr (VAR == DOCK_REDUCE_SHUFFLE) return wave_sum(v);
+    else if constexpr (VAR == DOCK_REDUCE_MFMA_F32) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        return mfma_tail(__builtin_amdgcn_mfma_f32_16x16x4f32(v, (lane_id() & 3) == 0 ? 1.f : 0.f, zero, 0, 0, 0)).x;
+    } else return sum4<VAR>(make_float4(v, 0.f, 0.f, 0.f)).x;
+}
+
 // ---------------------------------------------------------------------------
 // Ligand data held by a wave.
 // ---------------------------------------------------------------------------
@@ -303,6 +336,7 @@ struct Lig {
     int N, T, NF, G, n_batches, n_copies, max_depth;
     int stride;                     // accumulator stride (power of two >= N)
     int pmask;                      // stride * 16 - 1: slot byte offset -> position byte offset
+    int pbits;                      // its number of bits
     int wv;                         // wave of the individual (several waves per individual), else 0
     const u32x4* plist;             // pair records (dockblob::PairRec), n_batches x 64
     // per lane, per slot: atom a = lane + 64 * (slot + wv)
@@ -329,6 +363,7 @@ __device__ void load_ligand(const uint8_t* __restrict__ blob, Smem<SLOTS, WAVES>
     L.max_depth = uniform(h->max_depth);
     L.stride = uniform(h->slot_stride);
     L.pmask = L.stride * 16 - 1;
+    L.pbits = 31 - __builtin_clz(L.stride * 16);
     L.plist = uniform_ptr(reinterpret_cast<const u32x4*>(blob + h->off_plist));
     const float4* ref = reinterpret_cast<const float4*>(blob + h->off_ref);
     const float4* chg = reinterpret_cast<const float4*>(blob + h->off_chg);
@@ -340,10 +375,13 @@ __device__ void load_ligand(const uint8_t* __restrict__ blob, Smem<SLOTS, WAVES>
         const int ai = ok ? a : 0;
         float4 r = ref[ai], c = chg[ai];
         int4 ii = iv[ai];
-        L.y0[s][0] = r.x; L.y0[s][1] = r.y; L.y0[s][2] = r.z;
+        // lanes past the last atom sit at the rotation centre, in the root
+        // fragment and without charge: their position entries are zeros
+        // (unused pair lanes may read them)
+        L.y0[s][0] = ok ? r.x : 0.f; L.y0[s][1] = ok ? r.y : 0.f; L.y0[s][2] = ok ? r.z : 0.f;
         L.chg[s][0] = ok ? c.x : 0.f; L.chg[s][1] = ok ? c.y : 0.f; L.chg[s][2] = ok ? c.z : 0.f;
         L.cls[s] = ii.x;
-        L.frag[s] = ii.y;
+        L.frag[s] = ok ? ii.y : 0;
         L.orig[s] = ii.z;
     }
     const Torsion* tr = reinterpret_cast<const Torsion*>(blob + h->off_tors);
@@ -381,16 +419,6 @@ __device__ __forceinline__ float two_sum_fraction(float t, float node, float xl)
     return s2 + (e1 + e2);
 }
 
-// The fraction inside cell c (chosen when the loads were issued) along one
-// axis, and the world and box-clamped coordinates.
-__device__ __forceinline__ void axis_cell(float t, float xl, float lo, float hi, float h, float ih,
-                                          int c, float& f, float& xw, float& xc) {
-    xw = t + xl;
-    xc = fminf(fmaxf(xw, lo), hi);
-    const float node = lo + (float)c * h;
-    f = ((xw == xc) ? two_sum_fraction(t, node, xl) : (xc - node)) * ih;
-}
-
 // Corner values an atom reads: v[m][4 dz + 2 dy + dx] for the atom's type map
 // (m = 0), the electrostatic map (1) and the desolvation map (2). The loads
 // are issued early (grid_load) and consumed later (grid_term), so that their
@@ -401,8 +429,10 @@ struct GridTaps {
 };
 
 __device__ __forceinline__ int axis_index(float t, float xl, float lo, float hi, float ih, int n) {
-    const float xc = fminf(fmaxf(t + xl, lo), hi);
-    return min(max((int)floorf((xc - lo) * ih), 0), n - 2);
+    // the clamped point is not below lo, so truncation is the floor (a NaN
+    // converts to cell 0)
+    const float xc = __builtin_amdgcn_fmed3f(t + xl, lo, hi);
+    return (int)min((unsigned)((xc - lo) * ih), (unsigned)(n - 2));
 }
 
 // ANY_LAYOUT: the maps may be plain or corner-expanded (checked at run time);
@@ -486,32 +516,62 @@ __global__ __launch_bounds__(256) void expand_corners_kernel(GridParams G, f32x4
     }
 }
 
+// The atom's energy and gradient from its corner values. Poses mostly lie
+// inside the box: what only atoms outside it need (the fraction of the clamped
+// point, the penalty and the cut gradient) is skipped when the wave has none.
+template <bool XFIRST = false>
 __device__ __forceinline__ void grid_term(const GridParams& G, const GridTaps& tp, float q, float aq,
                                           const float xl[3], const float t[3],
                                           float& e, float& gx, float& gy, float& gz) {
-    float fx, fy, fz, xw, yw, zw, xc, yc, zc;
     const float ih = G.inv_spacing;
-    axis_cell(t[0], xl[0], G.origin[0], G.hi[0], G.spacing, ih, tp.cell[0], fx, xw, xc);
-    axis_cell(t[1], xl[1], G.origin[1], G.hi[1], G.spacing, ih, tp.cell[1], fy, yw, yc);
-    axis_cell(t[2], xl[2], G.origin[2], G.hi[2], G.spacing, ih, tp.cell[2], fz, zw, zc);
+    float f[3], out[3];
+    bool in[3];
+    bool all_in = true;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float node = fmaf((float)tp.cell[c], G.spacing, G.origin[c]);
+        f[c] = two_sum_fraction(t[c], node, xl[c]);
+        const float xw = t[c] + xl[c];
+        const float xc = __builtin_amdgcn_fmed3f(xw, G.origin[c], G.hi[c]);
+        in[c] = xw == xc;
+        all_in = all_in && in[c];
+    }
+    const bool any_out = __any(!all_in);
+    if (any_out) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float node = fmaf((float)tp.cell[c], G.spacing, G.origin[c]);
+            const float xw = t[c] + xl[c];
+            const float xc = __builtin_amdgcn_fmed3f(xw, G.origin[c], G.hi[c]);
+            f[c] = in[c] ? f[c] : xc - node;
+            out[c] = xw - xc;
+        }
+    }
+    const float fx = f[0] * ih, fy = f[1] * ih, fz = f[2] * ih;
     float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = tp.v[0][i] + q * tp.v[1][i] + aq * tp.v[2][i];
+    for (int i = 0; i < 8; ++i) v[i] = fmaf(aq, tp.v[2][i], fmaf(q, tp.v[1][i], tp.v[0][i]));
     // v index = 4 dz + 2 dy + dx
     const float d00 = v[1] - v[0], d01 = v[3] - v[2], d10 = v[5] - v[4], d11 = v[7] - v[6];
-    const float a00 = v[0] + fx * d00, a01 = v[2] + fx * d01;
-    const float a10 = v[4] + fx * d10, a11 = v[6] + fx * d11;
-    const float b0 = a00 + fy * (a01 - a00), b1 = a10 + fy * (a11 - a10);
-    const float val = b0 + fz * (b1 - b0);
+    const float a00 = fmaf(d00, fx, v[0]), a01 = fmaf(d01, fx, v[2]);
+    const float a10 = fmaf(d10, fx, v[4]), a11 = fmaf(d11, fx, v[6]);
+    const float ey0 = a01 - a00, ey1 = a11 - a10;
+    const float b0 = fmaf(fy, ey0, a00), b1 = fmaf(fy, ey1, a10);
     const float dfz = b1 - b0;
-    const float dfy = (a01 - a00) + fz * ((a11 - a10) - (a01 - a00));
-    const float dx0 = d00 + fy * (d01 - d00), dx1 = d10 + fy * (d11 - d10);
-    const float dfx = dx0 + fz * (dx1 - dx0);
-    const float ox = xw - xc, oy = yw - yc, oz = zw - zc;
-    e = val + kOut * (ox * ox + oy * oy + oz * oz);
-    gx = (xw == xc ? dfx * ih : 0.f) + 2.f * kOut * ox;
-    gy = (yw == yc ? dfy * ih : 0.f) + 2.f * kOut * oy;
-    gz = (zw == zc ? dfz * ih : 0.f) + 2.f * kOut * oz;
+    const float dfy = fmaf(fz, ey1 - ey0, ey0);
+    const float dx0 = fmaf(d01 - d00, fy, d00), dx1 = fmaf(d11 - d10, fy, d10);
+    const float dfx = fmaf(fz, dx1 - dx0, dx0);
+    e = fmaf(fz, dfz, b0);
+    gx = dfx * ih;
+    gy = dfy * ih;
+    gz = dfz * ih;
+    if (any_out) {
+        const float o2 = XFIRST ? fmaf(out[1], out[1], out[0] * out[0]) : fmaf(out[0], out[0], out[1] * out[1]);
+        e = fmaf(kOut, fmaf(out[2], out[2], o2), e);
+        gx = fmaf(2.f * kOut, out[0], in[0] ? gx : 0.f);
+        gy = fmaf(2.f * kOut, out[1], in[1] ? gy : 0.f);
+        gz = fmaf(2.f * kOut, out[2], in[2] ? gz : 0.f);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -521,12 +581,15 @@ __device__ __forceinline__ void grid_term(const GridParams& G, const GridTaps& t
 // (a, b, m) = (1, -2, 6), 12-10 hydrogen bond (5, -6, 10); r dE/dr is
 // -12 A / r^12 - m B / r^m. `live` masks pairs that are not kept (e = w = 0)
 // and `slope` masks the slope where r^2 is clamped (selects, so a masked
-// NaN or infinity gives 0 too).
+// NaN or infinity gives 0 too). XFIRST: the order in which the squares of the
+// separation are added, dy^2 before dx^2 or the other way round; the callers
+// fix it per pipeline step, since a different order rounds differently.
 // ---------------------------------------------------------------------------
 
+template <bool XFIRST>
 __device__ __forceinline__ void pair_term(float dx, float dy, float dz, float A, float B, bool hb,
                                           float qq, float ds, bool live, float& e, float& w) {
-    const float r2raw = dx * dx + dy * dy + dz * dz;
+    const float r2raw = fmaf(dz, dz, XFIRST ? fmaf(dy, dy, dx * dx) : fmaf(dx, dx, dy * dy));
     const bool slope = live && (r2raw >= kR2Min);
     const float r2 = fmaxf(r2raw, kR2Min);
     const float rinv = __builtin_amdgcn_rsqf(r2);
@@ -538,8 +601,8 @@ __device__ __forceinline__ void pair_term(float dx, float dy, float dz, float A,
     const float im = hb ? i6 * i4 : i6;
     const float t12 = A * i12;
     const float tm = B * im;
-    float elj = t12 + tm;
-    float dlj = -12.f * t12 + (hb ? -10.f : -6.f) * tm;                       // r dE/dr
+    float elj = fmaf(i12, A, tm);
+    float dlj = fmaf(hb ? -10.f : -6.f, tm, -(12.f * t12));                   // r dE/dr
     const bool capped = elj > kCap;
     elj = capped ? kCap : elj;
     dlj = capped ? 0.f : dlj;
@@ -553,12 +616,13 @@ __device__ __forceinline__ void pair_term(float dx, float dy, float dz, float A,
     const float q = __builtin_amdgcn_rcpf((r * D) * M);
     const float ired = (D * D) * q;
     const float eel = qq * ired;
-    // r dE/dr = -E (1 + r eps' / eps)
-    const float del = -eel * fmaf((r2 * ex) * q, kDielBKLB, 1.f);
+    // r dE/dr = -E (1 + r eps' / eps), with this factor
+    const float rel = fmaf((r2 * ex) * q, kDielBKLB, 1.f);
     // desolvation ds exp(-r^2 / (2 sigma^2)), r dE/dr = -E r^2 / sigma^2
-    const float eds = ds * __builtin_amdgcn_exp2f(-kDsInv2S2 * kLog2e * r2);
-    e = live ? elj + eel + eds : 0.f;
-    w = slope ? fmaf(eds, r2 * -kDsInvS2, dlj + del) * ir2 : 0.f;
+    const float eds0 = __builtin_amdgcn_exp2f(-kDsInv2S2 * kLog2e * r2);
+    const float eds = ds * eds0;
+    e = live ? fmaf(ds, eds0, fmaf(qq, ired, elj)) : 0.f;
+    w = slope ? fmaf(eds, r2 * -kDsInvS2, fmaf(-rel, eel, dlj)) * ir2 : 0.f;
 }
 
 // ---------------------------------------------------------------------------
@@ -576,6 +640,7 @@ struct IntC { static constexpr int value = V; };
 
 // Unused lanes (A = -0.0f) carry two slots no pair of their batch uses and
 // get zero energy and force, so every lane updates its slots.
+template <bool XFIRST = false>
 __device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj) {
     PairForce o;
     const uint32_t rec = pr.x;
@@ -584,7 +649,7 @@ __device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj) 
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
     const float qq = pi.w * pj.w;           // charges pre-scaled by sqrt(kElec)
     float e, w;
-    pair_term(dx, dy, dz, __uint_as_float(pr.y), __uint_as_float(pr.z), hb, qq,
+    pair_term<XFIRST>(dx, dy, dz, __uint_as_float(pr.y), __uint_as_float(pr.z), hb, qq,
               __uint_as_float(pr.w), valid, e, w);
     o.e = e;
     o.w = w;
@@ -611,11 +676,110 @@ __device__ __forceinline__ void store_force(float4* base, const PairForce& f, fl
 }
 
 // ---------------------------------------------------------------------------
+// Rigid-body and torsion arithmetic shared by the evaluations.
+// ---------------------------------------------------------------------------
+
+// Unit quaternion of the orientation genes and its rotation matrix.
+struct Rot {
+    float inv;                       // 1 / |q|
+    float w, x, y, z;
+    float m[9];
+};
+__device__ __forceinline__ Rot rotation(float w0, float x0, float y0, float z0) {
+    Rot r;
+    r.inv = __builtin_amdgcn_rsqf(fmaf(z0, z0, fmaf(y0, y0, fmaf(w0, w0, x0 * x0))));
+    r.w = w0 * r.inv; r.x = x0 * r.inv; r.y = y0 * r.inv; r.z = z0 * r.inv;
+    r.m[0] = fmaf(fmaf(r.y, r.y, r.z * r.z), -2.f, 1.f);
+    r.m[1] = 2.f * fmaf(r.x, r.y, -(r.w * r.z));
+    r.m[2] = 2.f * fmaf(r.x, r.z, r.w * r.y);
+    r.m[3] = 2.f * fmaf(r.x, r.y, r.w * r.z);
+    r.m[4] = fmaf(fmaf(r.x, r.x, r.z * r.z), -2.f, 1.f);
+    r.m[5] = 2.f * fmaf(r.y, r.z, -(r.w * r.x));
+    r.m[6] = 2.f * fmaf(r.x, r.z, -(r.w * r.y));
+    r.m[7] = 2.f * fmaf(r.y, r.z, r.w * r.x);
+    r.m[8] = fmaf(fmaf(r.x, r.x, r.y * r.y), -2.f, 1.f);
+    return r;
+}
+__device__ __forceinline__ void rotate(const Rot& R, float y0, float y1, float y2, float x[3]) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) x[r] = fmaf(R.m[3 * r + 2], y2, fmaf(R.m[3 * r + 1], y1, R.m[3 * r] * y0));
+}
+
+// Transform of one torsion, T(y) = R (y - p) + p about the unit axis u, as
+// three rows of a 3x4 matrix.
+__device__ __forceinline__ void torsion_transform(float psi, float4 p, float4 u, float4* rows) {
+    float sn, cs;
+    sincosf(psi, &sn, &cs);
+    const float oc = 1.f - cs;
+    const float ox = oc * u.x, oy = oc * u.y, oz = oc * u.z;
+    const float sx = sn * u.x, sy = sn * u.y, sz = sn * u.z;
+    const float R[9] = {fmaf(u.x, ox, cs), fmaf(u.y, ox, -sz), fmaf(u.z, ox, sy),
+                        fmaf(u.x, oy, sz), fmaf(u.y, oy, cs), fmaf(u.z, oy, -sx),
+                        fmaf(u.x, oz, -sy), fmaf(u.y, oz, sx), fmaf(u.z, oz, cs)};
+    const float at[3] = {p.x, p.y, p.z};
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        rows[r] = make_float4(R[3 * r], R[3 * r + 1], R[3 * r + 2],
+                              at[r] - fmaf(R[3 * r + 2], p.z, fmaf(R[3 * r], p.x, R[3 * r + 1] * p.y)));
+}
+// y <- T(y): one row is three FMAs, starting from the translation column.
+__device__ __forceinline__ void apply_transform(const float4 T[3], float& y0, float& y1, float& y2) {
+    const float z0 = fmaf(T[0].x, y0, fmaf(T[0].y, y1, fmaf(T[0].z, y2, T[0].w)));
+    const float z1 = fmaf(T[1].x, y0, fmaf(T[1].y, y1, fmaf(T[1].z, y2, T[1].w)));
+    const float z2 = fmaf(T[2].x, y0, fmaf(T[2].y, y1, fmaf(T[2].z, y2, T[2].w)));
+    y0 = z0; y1 = z1; y2 = z2;
+}
+
+// Gradient with respect to a torsion angle: the axis (from atom a to atom b)
+// times the torque about it, S_xg - x_a cross S_g, with S the sums of
+// (g, x cross g) over the atoms the torsion moves.
+__device__ __forceinline__ float torsion_gradient(const float S[6], float4 a, float4 b) {
+    float ux = b.x - a.x, uy = b.y - a.y, uz = b.z - a.z;
+    const float il = __builtin_amdgcn_rsqf(fmaf(uz, uz, fmaf(ux, ux, uy * uy)));
+    ux *= il; uy *= il; uz *= il;
+    const float mx = S[3] - fmaf(a.y, S[2], -(a.z * S[1]));
+    const float my = S[4] - fmaf(a.z, S[0], -(a.x * S[2]));
+    const float mz = S[5] - fmaf(a.x, S[1], -(a.y * S[0]));
+    return fmaf(uz, mz, fmaf(ux, mx, uy * my));
+}
+
+// This lane's gradient component from the totals: the force E/x (EG.y .. w)
+// for genes 0..2, (2/|q|) (0, tau) (x) q_hat with the torque tau for genes
+// 3..6, `gt` (the torsion gradient) from gene 7 on.
+__device__ __forceinline__ float gene_gradient(int gene, float4 EG, float4 TQ, const Rot& q, float gt) {
+    const float k2 = 2.0f * q.inv;
+    const float gw = -fmaf(TQ.z, q.z, fmaf(TQ.x, q.x, TQ.y * q.y));
+    const float gx = fmaf(q.w, TQ.x, fmaf(TQ.y, q.z, -(TQ.z * q.y)));
+    const float gy = fmaf(q.w, TQ.y, fmaf(TQ.z, q.x, -(TQ.x * q.z)));
+    const float gz = fmaf(q.w, TQ.z, fmaf(TQ.x, q.y, -(TQ.y * q.x)));
+    float gr = gt;
+    gr = gene == 0 ? EG.y : gr;
+    gr = gene == 1 ? EG.z : gr;
+    gr = gene == 2 ? EG.w : gr;
+    gr = gene == 3 ? k2 * gw : gr;
+    gr = gene == 4 ? k2 * gx : gr;
+    gr = gene == 5 ? k2 * gy : gr;
+    gr = gene == 6 ? k2 * gz : gr;
+    return gr;
+}
+
+// One ADADELTA step of a gene: running means of g^2 and dx^2, and the new
+// position (Zeiler 2012, Alg. 1).
+__device__ __forceinline__ float adadelta(float x, float gr, float rho, float eps, float& ag, float& ad) {
+    const float keep = 1.f - rho;
+    ag = fmaf(rho, ag, (keep * gr) * gr);
+    const float rate = -(__builtin_amdgcn_sqrtf(ad + eps) * __builtin_amdgcn_rsqf(ag + eps));
+    const float dx = rate * gr;
+    ad = fmaf(rho, ad, (keep * dx) * dx);
+    return fmaf(rate, gr, x);
+}
+
+// ---------------------------------------------------------------------------
 // One evaluation of E and dE/dgenotype for the individual held by this wave.
 // `gene` is gene `lane` (lanes >= G ignored); returns E (uniform) and writes
 // this lane's gradient component to `grad`.
 // ---------------------------------------------------------------------------
-template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true, bool GRAD = true>
+template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true, bool GRAD = true, bool TRIAL = false>
 __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L, float gene,
                           float& grad, float* atom_out) {
     const int lane = lane_id();
@@ -625,40 +789,12 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
     const float tx = readlane(gene, 0), ty = readlane(gene, 1), tz = readlane(gene, 2);
     const float qw0 = readlane(gene, 3), qx0 = readlane(gene, 4), qy0 = readlane(gene, 5),
                 qz0 = readlane(gene, 6);
-    const float qinv = __builtin_amdgcn_rsqf(qw0 * qw0 + qx0 * qx0 + qy0 * qy0 + qz0 * qz0);
-    const float qw = qw0 * qinv, qx = qx0 * qinv, qy = qy0 * qinv, qz = qz0 * qinv;
-    float Rq[9];
-    Rq[0] = 1.f - 2.f * (qy * qy + qz * qz);
-    Rq[1] = 2.f * (qx * qy - qw * qz);
-    Rq[2] = 2.f * (qx * qz + qw * qy);
-    Rq[3] = 2.f * (qx * qy + qw * qz);
-    Rq[4] = 1.f - 2.f * (qx * qx + qz * qz);
-    Rq[5] = 2.f * (qy * qz - qw * qx);
-    Rq[6] = 2.f * (qx * qz - qw * qy);
-    Rq[7] = 2.f * (qy * qz + qw * qx);
-    Rq[8] = 1.f - 2.f * (qx * qx + qy * qy);
+    const Rot Rq = rotation(qw0, qx0, qy0, qz0);
 
     // torsion transforms: T_k(y) = R_k (y - p) + p, about the reference axis
     const float psi = __shfl(gene, (7 + lane) & 63);
     if (lead && lane < L.T) {
-        float sn, cs;
-        sincosf(psi, &sn, &cs);
-        const float4 tp4 = sm.tor[lane][0], tu4 = sm.tor[lane][1];
-        const float tp[3] = {tp4.x, tp4.y, tp4.z};
-        const float ux = tu4.x, uy = tu4.y, uz = tu4.z;
-        const float oc = 1.f - cs;
-        float Rk[9];
-        Rk[0] = cs + oc * ux * ux;      Rk[1] = oc * ux * uy - sn * uz; Rk[2] = oc * ux * uz + sn * uy;
-        Rk[3] = oc * uy * ux + sn * uz; Rk[4] = cs + oc * uy * uy;      Rk[5] = oc * uy * uz - sn * ux;
-        Rk[6] = oc * uz * ux - sn * uy; Rk[7] = oc * uz * uy + sn * ux; Rk[8] = cs + oc * uz * uz;
-        float* o = sm.u.tk[lane];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            o[4 * r + 0] = Rk[3 * r + 0];
-            o[4 * r + 1] = Rk[3 * r + 1];
-            o[4 * r + 2] = Rk[3 * r + 2];
-            o[4 * r + 3] = tp[r] - (Rk[3 * r] * tp[0] + Rk[3 * r + 1] * tp[1] + Rk[3 * r + 2] * tp[2]);
-        }
+        torsion_transform(psi, sm.tor[lane][0], sm.tor[lane][1], reinterpret_cast<float4*>(sm.u.tk[lane]));
     } else if (lead && lane == kMaxTors) {
         float4* o = reinterpret_cast<float4*>(sm.u.tk[kMaxTors]);
         o[0] = make_float4(1.f, 0.f, 0.f, 0.f);
@@ -694,19 +830,10 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
             }
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                // one row = three FMAs, starting from the translation column
-                const float z0 = fmaf(T[q][0].x, y0, fmaf(T[q][0].y, y1, fmaf(T[q][0].z, y2, T[q][0].w)));
-                const float z1 = fmaf(T[q][1].x, y0, fmaf(T[q][1].y, y1, fmaf(T[q][1].z, y2, T[q][1].w)));
-                const float z2 = fmaf(T[q][2].x, y0, fmaf(T[q][2].y, y1, fmaf(T[q][2].z, y2, T[q][2].w)));
-                y0 = z0; y1 = z1; y2 = z2;
-            }
+            for (int q = 0; q < 2; ++q) apply_transform(T[q], y0, y1, y2);
         }
-#pragma unroll
-        for (int r = 0; r < 3; ++r) x[s][r] = Rq[3 * r] * y0 + Rq[3 * r + 1] * y1 + Rq[3 * r + 2] * y2;
-        // entries past the last atom hold zeros (unused pair lanes may read them)
-        sm.dyn[a] = a < N ? make_float4(x[s][0], x[s][1], x[s][2], kSqrtElec * L.chg[s][1])
-                          : make_float4(0.f, 0.f, 0.f, 0.f);
+        rotate(Rq, y0, y1, y2, x[s]);
+        sm.dyn[a] = make_float4(x[s][0], x[s][1], x[s][2], kSqrtElec * L.chg[s][1]);
     }
     lds_sync<WAVES>();
 
@@ -732,7 +859,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         const int nb = L.n_batches;
         const int pmask = L.pmask;
         auto pos_i = [&](uint32_t w) { return *slot(sm.dyn, w & pmask); };
-        auto pos_j = [&](uint32_t w) { return *slot(sm.dyn, (w >> dockblob::kSlotShift) & pmask); };
+        auto pos_j = [&](uint32_t w) { return *slot(sm.dyn, __builtin_amdgcn_ubfe(w, dockblob::kSlotShift, L.pbits)); };
         if (nb > 0) {
             const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<u32x4*>(L.plist), 0, nb * kWave * (int)sizeof(u32x4), kBufferWord3);
@@ -755,7 +882,9 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 Pi[n] = pos_i(rn.x);
                 Pj[n] = pos_j(rn.x);
                 __builtin_amdgcn_sched_barrier(0);   // keep the position reads at the step's start
-                e_lane += pair_force(R[r], Pi[c], Pj[c]).e;
+                constexpr bool last = decltype(load)::value == 0;
+                constexpr bool xfirst = (TRIAL && r == 0) || (last && r == 2);
+                e_lane += pair_force<xfirst>(R[r], Pi[c], Pj[c]).e;
                 if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
                 __builtin_amdgcn_sched_barrier(0);
                 ++k;
@@ -766,7 +895,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             using I3 = IntC<3>;
             using Load = IntC<1>;
             using NoLoad = IntC<0>;
-            while (k + 4 <= nb) { step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load()); }
+            while (k + (TRIAL ? 4 : 5) <= nb) { step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load()); }
             // the grid-map loads follow the last record load (global loads
             // complete in order)
             __builtin_amdgcn_sched_barrier(0);
@@ -776,6 +905,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             if (k < nb) step(I0(), NoLoad());
             if (k < nb) step(I1(), NoLoad());
             if (k < nb) step(I2(), NoLoad());
+            if constexpr (!TRIAL) if (k < nb) step(I3(), NoLoad());
         } else {
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s) grid_load<ANY_LAYOUT>(G, L.cls[s], x[s], tv, tap[s]);
@@ -788,7 +918,11 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         // ceil(n_batches / WAVES) batches (the last runs may be short or empty)
         const int nslot = L.n_copies * L.stride;
         float4* const accw = sm.u.acc + (WAVES == 1 ? 0 : L.wv * nslot);
-        for (int k = lane; k < nslot; k += kWave) accw[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // cleared by whole waves of slots (the array holds a multiple of 64;
+        // a wave's last store may clear slots of the next wave's range, which
+        // nobody has added to yet)
+        static_assert(Smem<SLOTS, WAVES>::kSlots % kWave == 0, "clearing stays inside the accumulators");
+        for (int k = 0; k < nslot; k += kWave) accw[k + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
         lds_sync<WAVES>();
         const int nb_all = L.n_batches;
         const int run = (nb_all + WAVES - 1) / WAVES;
@@ -798,7 +932,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         const int pmask = L.pmask;
         // an atom's position sits at its slot's byte offset masked to one stride
         auto pos_i = [&](uint32_t w) { return *slot(sm.dyn, w & pmask); };
-        auto pos_j = [&](uint32_t w) { return *slot(sm.dyn, (w >> dockblob::kSlotShift) & pmask); };
+        auto pos_j = [&](uint32_t w) { return *slot(sm.dyn, __builtin_amdgcn_ubfe(w, dockblob::kSlotShift, L.pbits)); };
         // Software pipeline over batches with no branch inside. Step k
         // stores batch k (its slot values were read in step k - 1) and
         // computes batch k + 1 while reading the positions of batch k + 2
@@ -844,7 +978,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 Pj[c] = pos_j(rf.x);
                 if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
                 __builtin_amdgcn_sched_barrier(0);   // keep the loads at the step's start
-                F[n] = pair_force(R[(r + 1) & 3], Pi[n], Pj[n]);
+                F[n] = pair_force<r == 1 && decltype(load)::value == 0>(R[(r + 1) & 3], Pi[n], Pj[n]);
                 store_force(accw, F[c], Ai[c], Aj[c]);
                 e_lane += F[c].e;
                 Ai[n] = *slot(accw, F[n].si);
@@ -904,7 +1038,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
     for (int s = 0; s < SLOTS; ++s) {
         const int a = lane + kWave * (s + L.wv);
         float e, gx, gy, gz;
-        grid_term(G, tap[s], L.chg[s][1], L.chg[s][2], x[s], tv, e, gx, gy, gz);
+        grid_term<TRIAL>(G, tap[s], L.chg[s][1], L.chg[s][2], x[s], tv, e, gx, gy, gz);
         const bool ok = a < N;
         e_atom[s] = ok ? e : 0.f;
         g[s][0] += ok ? gx : 0.f;
@@ -912,21 +1046,16 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         g[s][2] += ok ? gz : 0.f;
         e_lane += e_atom[s];
     }
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s)
-        if (lane + kWave * (s + L.wv) >= N) { g[s][0] = g[s][1] = g[s][2] = 0.f; }
-
     if constexpr (!GRAD) {
         // the block sum of E alone, in the chosen variant
         grad = 0.f;
         lds_sync<WAVES>();   // the next evaluation rewrites the position table
-        return sum4<VAR>(make_float4(e_lane, 0.f, 0.f, 0.f)).x;
+        return sum1<VAR>(e_lane);
     }
 
     // block sum of {E, gx, gy, gz}: the paper's reduction, in the chosen variant
-    float4 eg = make_float4(e_lane, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) { eg.y += g[s][0]; eg.z += g[s][1]; eg.w += g[s][2]; }
+    float4 eg = make_float4(e_lane, g[0][0], g[0][1], g[0][2]);
+    if constexpr (SLOTS == 2) { eg.y += g[1][0]; eg.z += g[1][1]; eg.w += g[1][2]; }
     float4 EG = sum4<VAR>(eg);
 
     // torsion torques: prefix sums of (g, x cross g) in depth-first order;
@@ -935,14 +1064,15 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         P[s][0] = g[s][0]; P[s][1] = g[s][1]; P[s][2] = g[s][2];
-        P[s][3] = x[s][1] * g[s][2] - x[s][2] * g[s][1];
-        P[s][4] = x[s][2] * g[s][0] - x[s][0] * g[s][2];
-        P[s][5] = x[s][0] * g[s][1] - x[s][1] * g[s][0];
+        P[s][3] = fmaf(x[s][1], g[s][2], -(x[s][2] * g[s][1]));
+        P[s][4] = fmaf(x[s][2], g[s][0], -(x[s][0] * g[s][2]));
+        P[s][5] = fmaf(x[s][0], g[s][1], -(x[s][1] * g[s][0]));
     }
+    wave_scan6(P[0]);
+    if constexpr (SLOTS == 2) {
+        wave_scan6(P[1]);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        P[0][c] = wave_scan(P[0][c]);
-        if constexpr (SLOTS == 2) P[1][c] = wave_scan(P[1][c]) + readlane(P[0][c], 63);
+        for (int c = 0; c < 6; ++c) P[1][c] += readlane(P[0][c], 63);
     }
     float4 TQ = make_float4(readlane(P[SLOTS - 1][3], 63), readlane(P[SLOTS - 1][4], 63),
                             readlane(P[SLOTS - 1][5], 63), 0.f);
@@ -999,36 +1129,10 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 S[c] = ph - pl;
             }
         }
-        const float4 xa = sm.dyn[t_apos];
-        const float4 xb = sm.dyn[t_bpos];
-        float ux = xb.x - xa.x, uy = xb.y - xa.y, uz = xb.z - xa.z;
-        const float il = __builtin_amdgcn_rsqf(ux * ux + uy * uy + uz * uz);
-        ux *= il; uy *= il; uz *= il;
-        // S_xg - x_a cross S_g
-        const float mx = S[3] - (xa.y * S[2] - xa.z * S[1]);
-        const float my = S[4] - (xa.z * S[0] - xa.x * S[2]);
-        const float mz = S[5] - (xa.x * S[1] - xa.y * S[0]);
-        gpsi = (lane < L.T) ? ux * mx + uy * my + uz * mz : 0.f;
+        const float gt = torsion_gradient(S, sm.dyn[t_apos], sm.dyn[t_bpos]);
+        gpsi = lane < L.T ? gt : 0.f;
     }
-    // gradient with respect to the genotype
-    {
-        // (2/|q|) (0, tau) (x) q_hat
-        const float k2 = 2.0f * qinv;
-        const float gw = -(TQ.x * qx + TQ.y * qy + TQ.z * qz);
-        const float gqx = qw * TQ.x + (TQ.y * qz - TQ.z * qy);
-        const float gqy = qw * TQ.y + (TQ.z * qx - TQ.x * qz);
-        const float gqz = qw * TQ.z + (TQ.x * qy - TQ.y * qx);
-        const float gt = __shfl(gpsi, (lane - 7) & 63);
-        float gr = gt;
-        gr = lane == 0 ? EG.y : gr;
-        gr = lane == 1 ? EG.z : gr;
-        gr = lane == 2 ? EG.w : gr;
-        gr = lane == 3 ? k2 * gw : gr;
-        gr = lane == 4 ? k2 * gqx : gr;
-        gr = lane == 5 ? k2 * gqy : gr;
-        gr = lane == 6 ? k2 * gqz : gr;
-        grad = gr;
-    }
+    grad = gene_gradient(lane, EG, TQ, Rq, __shfl(gpsi, (lane - 7) & 63));
     if (atom_out) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
@@ -1053,12 +1157,16 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
 // blockIdx.x + gridDim.x, ... (independent evaluations, so a static stride
 // gives the same results as any other assignment). ANY_LAYOUT: the maps may
 // be plain or corner-expanded; otherwise the corner-expanded copy is bound.
-template <int SLOTS, int VAR, bool ANY_LAYOUT>
-__global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void score_kernel(GridParams G, const uint8_t* __restrict__ blob,
-                                                   int n, const float* __restrict__ gen,
-                                                   float* __restrict__ energy,
-                                                   float* __restrict__ grad,
-                                                   float* __restrict__ atom_out) {
+// GRAD = false, for calls that ask for neither a gradient nor the per-atom
+// output: the energy-only evaluation, same energies bit for bit. It is bound
+// by VALU issue like the full one but issues 0.6 of its instructions, and at
+// its 114 registers four waves fit a SIMD instead of three: 50,001 genotypes
+// of a 48-atom ligand took 139 us with the gradient made and dropped, 90 us so;
+// 65,536 of a 24-atom one 100 and 52 us, two per wave 65 and 40 us.
+template <int SLOTS, int VAR, bool ANY_LAYOUT, bool GRAD>
+__global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void score_kernel(
+    GridParams G, const uint8_t* __restrict__ blob, int n, const float* __restrict__ gen, float* __restrict__ energy,
+    float* __restrict__ grad, float* __restrict__ atom_out) {
     __shared__ Smem<SLOTS> sm;
     Lig<SLOTS> L;
     load_ligand<SLOTS>(blob, sm, L);
@@ -1067,10 +1175,10 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void score_kernel(GridPar
     for (int ind = blockIdx.x; ind < n; ind += gridDim.x) {
         const float gene = lane < G_ ? gen[(size_t)ind * G_ + lane] : 0.f;
         float gr;
-        float* ao = atom_out ? atom_out + (size_t)ind * L.N * 8 : nullptr;
-        const float E = evaluate<SLOTS, VAR, 1, ANY_LAYOUT>(G, sm, L, gene, gr, ao);
+        float* ao = GRAD && atom_out ? atom_out + (size_t)ind * L.N * 8 : nullptr;
+        const float E = evaluate<SLOTS, VAR, 1, ANY_LAYOUT, GRAD>(G, sm, L, gene, gr, ao);
         if (lane == 0) energy[ind] = E;
-        if (grad && lane < G_) grad[(size_t)ind * G_ + lane] = gr;
+        if (GRAD && grad && lane < G_) grad[(size_t)ind * G_ + lane] = gr;
     }
 }
 
@@ -1079,14 +1187,10 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void score_kernel(GridPar
 // trial x + bias + dev, else x - bias - dev, accepted when its energy is lower;
 // bias and the step scale rho follow the outcome. One wave per individual,
 // gene `lane`; energies only (the gradient evaluate() also makes is unused).
-// State updates are float32 in a fixed order with no fused operations
-// (contraction is off in this kernel; evaluate() keeps its own FMAs).
+// State updates are float32 in a fixed order with no fused operations.
 template <int SLOTS, int VAR>
 __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void sw_kernel(GridParams G, const uint8_t* __restrict__ blob,
                                                 docklaunch::SwParams p) {
-    // no product below may be fused into an add (FMA): the state must round
-    // after every operation
-#pragma clang fp contract(off)
     __shared__ Smem<SLOTS> sm;
     Lig<SLOTS> L;
     load_ligand<SLOTS>(blob, sm, L);
@@ -1110,7 +1214,7 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void sw_kernel(GridParams
         for (int t = 0; t < 2; ++t) {      // uniform: E and the trial energies are wave-uniform
             const float c = t == 0 ? (x + b) + dev : (x - b) - dev;
             float gr;
-            const float Et = evaluate<SLOTS, VAR, 1, true, false>(G, sm, L, c, gr, nullptr);
+            const float Et = evaluate<SLOTS, VAR, 1, true, false, true>(G, sm, L, c, gr, nullptr);
             if (t == 0) e_try0 = Et; else e_try1 = Et;
             if (Et < E) {
                 x = c;
@@ -1181,13 +1285,11 @@ __device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>&
         lastG = gr;
         if (E < bestE) { bestE = E; bx = x; }
         gr = act ? gr : 0.f;
-        ag = rho * ag + (1.f - rho) * gr * gr;
-        const float dx = -(__builtin_amdgcn_sqrtf(ad + eps) * __builtin_amdgcn_rsqf(ag + eps)) * gr;
-        ad = rho * ad + (1.f - rho) * dx * dx;
-        float xn = x + dx;
+        float xn = adadelta(x, gr, rho, eps, ag, ad);
         const bool isq = lane >= 3 && lane < 7;
         const float q2 = isq ? xn * xn : 0.f;
-        const float nq2 = (readlane(q2, 3) + readlane(q2, 4)) + (readlane(q2, 5) + readlane(q2, 6));
+        // genes 3..6 share the first row; the other rows' lanes discard it
+        const float nq2 = (row_lane<3>(q2) + row_lane<4>(q2)) + (row_lane<5>(q2) + row_lane<6>(q2));
         if (isq) xn = (nq2 >= 1e-12f) ? xn * __builtin_amdgcn_rsqf(nq2) : x;
         x = act ? xn : 0.f;
     }
@@ -1352,47 +1454,56 @@ constexpr int kHalf = 32;
 // fit in the CU's 160 KB after each block's LDS is rounded up to the
 // allocation granularity: 12,800 bytes per block fit, while the 13,344 bytes
 // of accumulators sized for 320 slots per half left room for eleven blocks
-// per CU. A ligand of <= 32 atoms needs at most 288 slots.
-struct __align__(16) Smem2 {
+// per CU. A ligand of <= 32 atoms needs at most 288 slots; an energy-only
+// evaluation none (FORCES = false: sixteen blocks, four waves per SIMD).
+template <bool FORCES>
+struct __align__(16) Smem2T {
     float4 dyn[2][kHalf];               // per half: positions relative to t, sqrt(kElec) q
     union {
         float tk[2][kMaxTors + 1][12];  // per half: torsion transforms, identity at kMaxTors
-        float4 acc[2][dockblob::kMaxSlotsTiny];   // per half: pair-force accumulators
+        float4 acc[2][FORCES ? dockblob::kMaxSlotsTiny : 1];   // per half: pair-force accumulators
     } u;
     float4 tor[kMaxTors][2];
     uint32_t chain[kMaxFrag][kChain / 4];
 };
+using Smem2 = Smem2T<true>;
 static_assert(sizeof(Smem2) <= 12800, "twelve two-individual blocks per CU");
 
-__device__ __forceinline__ float hsel(float a, float b) { return lane_id() < kHalf ? a : b; }
-
-// Lane c of this lane's half.
-__device__ __forceinline__ float half_lane(float v, int c) { return hsel(readlane(v, c), readlane(v, kHalf + c)); }
-
-// Sum over this lane's half, every lane of the half receives it: row sums by
-// a DPP butterfly, then row 0 into row 1 and row 2 into row 3.
-__device__ __forceinline__ float half_sum(float v) {
-    v += dpp<0xB1>(v);         // quad_perm [1,0,3,2]
-    v += dpp<0x4E>(v);         // quad_perm [2,3,0,1]
-    v += dpp<0x141>(v);        // row_half_mirror
-    v += dpp<0x140>(v);        // row_mirror
-    v += dpp<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    return hsel(readlane(v, kHalf - 1), readlane(v, 2 * kHalf - 1));
+// Exchanges the second and fourth row of `lo` with the first and third of
+// `hi`: from two copies of a value, `lo` then holds each half's first row in
+// both of the half's rows, `hi` its second.
+#define SWAP_ROWS(lo, hi) "v_permlane16_swap_b32 " lo ", " hi "\n\t"
+__device__ __forceinline__ void half_rows(float v, float& lo, float& hi) {
+    lo = hi = v;
+    asm("s_nop 1\n\t" SWAP_ROWS("%0", "%1") "s_nop 1" : "+v"(lo), "+v"(hi));
 }
 
-// Inclusive prefix sum within each half.
-__device__ __forceinline__ float half_scan(float v) {
-    v += dpp<0x111>(v);          // row_shr:1
-    v += dpp<0x112>(v);          // row_shr:2
-    v += dpp<0x114>(v);          // row_shr:4
-    v += dpp<0x118>(v);          // row_shr:8
-    v += dpp<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
-    return v;
+// Sums over this lane's half, every lane of the half receives them: row sums
+// by a DPP butterfly, then the half's two rows.
+__device__ __forceinline__ float half_sum(float v) {
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP1) : "+v"(v));
+    float lo, hi;
+    half_rows(v, lo, hi);
+    return lo + hi;
+}
+__device__ __forceinline__ float4 half_sum4(float4 v) {
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    float4 w = v;
+    asm("s_nop 1\n\t" SWAP_ROWS("%0", "%4") SWAP_ROWS("%1", "%5") SWAP_ROWS("%2", "%6") SWAP_ROWS("%3", "%7") "s_nop 1"
+        : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w), "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));
+    return make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+}
+
+// Inclusive prefix sums of six values within each half.
+__device__ __forceinline__ void half_scan6(float v[6]) {
+    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_HALF(DPP_STEP6)
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
 }
 
 // The ligand as a two-individual wave holds it: lane j of either half the
 // atom j (per-lane registers), the shared torsion and fragment tables in LDS.
-__device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2& sm, Lig<1>& L, bool fill_lds = true) {
+template <bool FORCES>
+__device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2T<FORCES>& sm, Lig<1>& L, bool fill_lds = true) {
     if (fill_lds) wave_sync();  // previous users of the LDS tables are done
     const Header* h = reinterpret_cast<const Header*>(blob);
     const int lane = lane_id();
@@ -1406,6 +1517,7 @@ __device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2& sm, Lig<1>
     L.max_depth = uniform(h->max_depth);
     L.stride = uniform(h->slot_stride);
     L.pmask = L.stride * 16 - 1;
+    L.pbits = 31 - __builtin_clz(L.stride * 16);
     L.plist = uniform_ptr(reinterpret_cast<const u32x4*>(blob + h->off_plist));
     const float4* ref = reinterpret_cast<const float4*>(blob + h->off_ref);
     const float4* chg = reinterpret_cast<const float4*>(blob + h->off_chg);
@@ -1415,10 +1527,10 @@ __device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2& sm, Lig<1>
     const int ai = ok ? a : 0;
     const float4 r = ref[ai], c = chg[ai];
     const int4 ii = iv[ai];
-    L.y0[0][0] = r.x; L.y0[0][1] = r.y; L.y0[0][2] = r.z;
+    L.y0[0][0] = ok ? r.x : 0.f; L.y0[0][1] = ok ? r.y : 0.f; L.y0[0][2] = ok ? r.z : 0.f;
     L.chg[0][0] = ok ? c.x : 0.f; L.chg[0][1] = ok ? c.y : 0.f; L.chg[0][2] = ok ? c.z : 0.f;
     L.cls[0] = ii.x;
-    L.frag[0] = ii.y;
+    L.frag[0] = ok ? ii.y : 0;
     L.orig[0] = ii.z;
     const Torsion* tr = reinterpret_cast<const Torsion*>(blob + h->off_tors);
     if (fill_lds && lane < L.T) {
@@ -1440,51 +1552,23 @@ __device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2& sm, Lig<1>
 // ignored); returns this half's E and writes this lane's gradient component
 // to `grad`. atom_out: this half's per-atom output (or nullptr).
 template <bool ANY_LAYOUT, bool GRAD = true>
-__device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, float gene, float& grad,
+__device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& L, float gene, float& grad,
                            float* atom_out) {
     const int lane = lane_id();
     const int j = lane & (kHalf - 1);
     const int h = lane >> 5;
     const int hb = h * kHalf;
     const int N = L.N;
-    const float tx = half_lane(gene, 0), ty = half_lane(gene, 1), tz = half_lane(gene, 2);
-    const float qw0 = half_lane(gene, 3), qx0 = half_lane(gene, 4), qy0 = half_lane(gene, 5),
-                qz0 = half_lane(gene, 6);
-    const float qinv = __builtin_amdgcn_rsqf(qw0 * qw0 + qx0 * qx0 + qy0 * qy0 + qz0 * qz0);
-    const float qw = qw0 * qinv, qx = qx0 * qinv, qy = qy0 * qinv, qz = qz0 * qinv;
-    float Rq[9];
-    Rq[0] = 1.f - 2.f * (qy * qy + qz * qz);
-    Rq[1] = 2.f * (qx * qy - qw * qz);
-    Rq[2] = 2.f * (qx * qz + qw * qy);
-    Rq[3] = 2.f * (qx * qy + qw * qz);
-    Rq[4] = 1.f - 2.f * (qx * qx + qz * qz);
-    Rq[5] = 2.f * (qy * qz - qw * qx);
-    Rq[6] = 2.f * (qx * qz - qw * qy);
-    Rq[7] = 2.f * (qy * qz + qw * qx);
-    Rq[8] = 1.f - 2.f * (qx * qx + qy * qy);
+    float body, rest;                            // the rigid-body genes lie in the half's first row
+    half_rows(gene, body, rest);
+    const float tx = row_lane<0>(body), ty = row_lane<1>(body), tz = row_lane<2>(body);
+    const Rot Rq = rotation(row_lane<3>(body), row_lane<4>(body), row_lane<5>(body), row_lane<6>(body));
 
     // torsion transforms of this half's individual (T <= 25, so lane 31 of
     // each half is free to write the identity)
     const float psi = __shfl(gene, hb + ((7 + j) & (kHalf - 1)));
     if (j < L.T) {
-        float sn, cs;
-        sincosf(psi, &sn, &cs);
-        const float4 tp4 = sm.tor[j][0], tu4 = sm.tor[j][1];
-        const float tp[3] = {tp4.x, tp4.y, tp4.z};
-        const float ux = tu4.x, uy = tu4.y, uz = tu4.z;
-        const float oc = 1.f - cs;
-        float Rk[9];
-        Rk[0] = cs + oc * ux * ux;      Rk[1] = oc * ux * uy - sn * uz; Rk[2] = oc * ux * uz + sn * uy;
-        Rk[3] = oc * uy * ux + sn * uz; Rk[4] = cs + oc * uy * uy;      Rk[5] = oc * uy * uz - sn * ux;
-        Rk[6] = oc * uz * ux - sn * uy; Rk[7] = oc * uz * uy + sn * ux; Rk[8] = cs + oc * uz * uz;
-        float* o = sm.u.tk[h][j];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            o[4 * r + 0] = Rk[3 * r + 0];
-            o[4 * r + 1] = Rk[3 * r + 1];
-            o[4 * r + 2] = Rk[3 * r + 2];
-            o[4 * r + 3] = tp[r] - (Rk[3 * r] * tp[0] + Rk[3 * r + 1] * tp[1] + Rk[3 * r + 2] * tp[2]);
-        }
+        torsion_transform(psi, sm.tor[j][0], sm.tor[j][1], reinterpret_cast<float4*>(sm.u.tk[h][j]));
     } else if (j == kHalf - 1) {
         float4* o = reinterpret_cast<float4*>(sm.u.tk[h][kMaxTors]);
         o[0] = make_float4(1.f, 0.f, 0.f, 0.f);
@@ -1511,18 +1595,10 @@ __device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, floa
                 T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
             }
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float z0 = fmaf(T[q][0].x, y0, fmaf(T[q][0].y, y1, fmaf(T[q][0].z, y2, T[q][0].w)));
-                const float z1 = fmaf(T[q][1].x, y0, fmaf(T[q][1].y, y1, fmaf(T[q][1].z, y2, T[q][1].w)));
-                const float z2 = fmaf(T[q][2].x, y0, fmaf(T[q][2].y, y1, fmaf(T[q][2].z, y2, T[q][2].w)));
-                y0 = z0; y1 = z1; y2 = z2;
-            }
+            for (int q = 0; q < 2; ++q) apply_transform(T[q], y0, y1, y2);
         }
-#pragma unroll
-        for (int r = 0; r < 3; ++r) x[r] = Rq[3 * r] * y0 + Rq[3 * r + 1] * y1 + Rq[3 * r + 2] * y2;
-        // entries past the last atom hold zeros (unused pair lanes may read them)
-        sm.dyn[h][j] = j < N ? make_float4(x[0], x[1], x[2], kSqrtElec * L.chg[0][1])
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
+        rotate(Rq, y0, y1, y2, x);
+        sm.dyn[h][j] = make_float4(x[0], x[1], x[2], kSqrtElec * L.chg[0][1]);
     }
     wave_sync();
 
@@ -1533,10 +1609,11 @@ __device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, floa
     float4* const acch = sm.u.acc[h];
     const int pmask = L.pmask;
     auto pos_i = [&](uint32_t w) { return *slot(dynh, w & pmask); };
-    auto pos_j = [&](uint32_t w) { return *slot(dynh, (w >> dockblob::kSlotShift) & pmask); };
+    auto pos_j = [&](uint32_t w) { return *slot(dynh, __builtin_amdgcn_ubfe(w, dockblob::kSlotShift, L.pbits)); };
     if constexpr (GRAD) {
         const int nslot = L.n_copies * L.stride;
-        for (int k = j; k < nslot; k += kHalf) acch[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        static_assert(dockblob::kMaxSlotsTiny % kHalf == 0, "clearing stays inside the half's accumulators");
+        for (int k = 0; k < nslot; k += kHalf) acch[k + j] = make_float4(0.f, 0.f, 0.f, 0.f);
         wave_sync();
     }
     // pair terms: step s takes records 32 (s % 2) .. 32 (s % 2) + 31 of
@@ -1568,7 +1645,7 @@ __device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, floa
             Pi[n] = pos_i(rn.x);
             Pj[n] = pos_j(rn.x);
             __builtin_amdgcn_sched_barrier(0);
-            const PairForce F = pair_force(R[r], Pi[c], Pj[c]);
+            const PairForce F = pair_force<r == 0 || (decltype(load)::value == 0 && r == 2)>(R[r], Pi[c], Pj[c]);
             if constexpr (GRAD) {
                 const float4 ai = *slot(acch, F.si);
                 const float4 aj = *slot(acch, F.sj);
@@ -1624,18 +1701,19 @@ __device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, floa
         return half_sum(e_lane);
     }
     // block sum of {E, gx, gy, gz} over each half (wavefront shuffle)
-    const float4 EG = make_float4(half_sum(e_lane), half_sum(g[0]), half_sum(g[1]), half_sum(g[2]));
+    const float4 EG = half_sum4(make_float4(e_lane, g[0], g[1], g[2]));
     // torsion torques: prefix sums of (g, x cross g) within each half; the
     // half's last lane gives the torque about t
     float P[6];
     P[0] = g[0]; P[1] = g[1]; P[2] = g[2];
-    P[3] = x[1] * g[2] - x[2] * g[1];
-    P[4] = x[2] * g[0] - x[0] * g[2];
-    P[5] = x[0] * g[1] - x[1] * g[0];
+    P[3] = fmaf(x[1], g[2], -(x[2] * g[1]));
+    P[4] = fmaf(x[2], g[0], -(x[0] * g[2]));
+    P[5] = fmaf(x[0], g[1], -(x[1] * g[0]));
+    half_scan6(P);
+    float lo, tq[3];                             // the half's last lane lies in its second row
 #pragma unroll
-    for (int c = 0; c < 6; ++c) P[c] = half_scan(P[c]);
-    const float4 TQ = make_float4(half_lane(P[3], kHalf - 1), half_lane(P[4], kHalf - 1),
-                                  half_lane(P[5], kHalf - 1), 0.f);
+    for (int c = 0; c < 3; ++c) half_rows(P[3 + c], lo, tq[c]);
+    const float4 TQ = make_float4(row_lane<15>(tq[0]), row_lane<15>(tq[1]), row_lane<15>(tq[2]), 0.f);
     float gpsi = 0.f;
     {
         const int pk = j < L.T ? __float_as_int(sm.tor[j][0].w) : (1 << 16) | (1 << 24);
@@ -1645,33 +1723,10 @@ __device__ float evaluate2(const GridParams& G, Smem2& sm, const Lig<1>& L, floa
 #pragma unroll
         for (int c = 0; c < 6; ++c)
             S[c] = __shfl(P[c], hb + (hi & (kHalf - 1))) - __shfl(P[c], hb + (lo & (kHalf - 1)));
-        const float4 xa = dynh[t_apos & (kHalf - 1)];
-        const float4 xb = dynh[t_bpos & (kHalf - 1)];
-        float ux = xb.x - xa.x, uy = xb.y - xa.y, uz = xb.z - xa.z;
-        const float il = __builtin_amdgcn_rsqf(ux * ux + uy * uy + uz * uz);
-        ux *= il; uy *= il; uz *= il;
-        const float mx = S[3] - (xa.y * S[2] - xa.z * S[1]);
-        const float my = S[4] - (xa.z * S[0] - xa.x * S[2]);
-        const float mz = S[5] - (xa.x * S[1] - xa.y * S[0]);
-        gpsi = (j < L.T) ? ux * mx + uy * my + uz * mz : 0.f;
+        const float gt = torsion_gradient(S, dynh[t_apos & (kHalf - 1)], dynh[t_bpos & (kHalf - 1)]);
+        gpsi = j < L.T ? gt : 0.f;
     }
-    {
-        const float k2 = 2.0f * qinv;
-        const float gw = -(TQ.x * qx + TQ.y * qy + TQ.z * qz);
-        const float gqx = qw * TQ.x + (TQ.y * qz - TQ.z * qy);
-        const float gqy = qw * TQ.y + (TQ.z * qx - TQ.x * qz);
-        const float gqz = qw * TQ.z + (TQ.x * qy - TQ.y * qx);
-        const float gt = __shfl(gpsi, hb + ((j - 7) & (kHalf - 1)));
-        float gr = gt;
-        gr = j == 0 ? EG.y : gr;
-        gr = j == 1 ? EG.z : gr;
-        gr = j == 2 ? EG.w : gr;
-        gr = j == 3 ? k2 * gw : gr;
-        gr = j == 4 ? k2 * gqx : gr;
-        gr = j == 5 ? k2 * gqy : gr;
-        gr = j == 6 ? k2 * gqz : gr;
-        grad = gr;
-    }
+    grad = gene_gradient(j, EG, TQ, Rq, __shfl(gpsi, hb + ((j - 7) & (kHalf - 1))));
     if (atom_out && j < N) {
         float4* o = reinterpret_cast<float4*>(atom_out) + 2 * L.orig[0];
         o[0] = make_float4(x[0], x[1], x[2], e_atom);
@@ -1708,13 +1763,10 @@ __device__ void local_search_two(const DevItem& it, int ind0, int count, Smem2& 
         lastG = gr;
         if (E < bestE) { bestE = E; bx = x; }
         gr = act ? gr : 0.f;
-        ag = rho * ag + (1.f - rho) * gr * gr;
-        const float dx = -(__builtin_amdgcn_sqrtf(ad + eps) * __builtin_amdgcn_rsqf(ag + eps)) * gr;
-        ad = rho * ad + (1.f - rho) * dx * dx;
-        float xn = x + dx;
+        float xn = adadelta(x, gr, rho, eps, ag, ad);
         const bool isq = j >= 3 && j < 7;
         const float q2 = isq ? xn * xn : 0.f;
-        const float nq2 = (half_lane(q2, 3) + half_lane(q2, 4)) + (half_lane(q2, 5) + half_lane(q2, 6));
+        const float nq2 = (row_lane<3>(q2) + row_lane<4>(q2)) + (row_lane<5>(q2) + row_lane<6>(q2));
         if (isq) xn = (nq2 >= 1e-12f) ? xn * __builtin_amdgcn_rsqf(nq2) : x;
         x = act ? xn : 0.f;
     }
@@ -1835,13 +1887,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 }
 
 // Persistent scoring kernel, two genotypes per wave (ind = 2 k + half).
-template <bool ANY_LAYOUT>
-__global__ __launch_bounds__(64, 3) void score_kernel_two(GridParams G, const uint8_t* __restrict__ blob, int n,
+template <bool ANY_LAYOUT, bool GRAD>
+__global__ __launch_bounds__(64, GRAD ? 3 : 4) void score_kernel_two(GridParams G, const uint8_t* __restrict__ blob, int n,
                                                           const float* __restrict__ gen,
                                                           float* __restrict__ energy,
                                                           float* __restrict__ grad,
                                                           float* __restrict__ atom_out) {
-    __shared__ Smem2 sm;
+    __shared__ Smem2T<GRAD> sm;
     Lig<1> L;
     load_ligand2(blob, sm, L);
     const int lane = lane_id();
@@ -1854,10 +1906,10 @@ __global__ __launch_bounds__(64, 3) void score_kernel_two(GridParams G, const ui
         const int ind = live ? 2 * k + h : 2 * k;
         const float gene = j < G_ ? gen[(size_t)ind * G_ + j] : 0.f;
         float gr;
-        float* ao = (atom_out && live) ? atom_out + (size_t)ind * L.N * 8 : nullptr;
-        const float E = evaluate2<ANY_LAYOUT>(G, sm, L, gene, gr, ao);
+        float* ao = (GRAD && atom_out && live) ? atom_out + (size_t)ind * L.N * 8 : nullptr;
+        const float E = evaluate2<ANY_LAYOUT, GRAD>(G, sm, L, gene, gr, ao);
         if (live && j == 0) energy[ind] = E;
-        if (live && grad && j < G_) grad[(size_t)ind * G_ + j] = gr;
+        if (GRAD && live && grad && j < G_) grad[(size_t)ind * G_ + j] = gr;
     }
 }
 
@@ -1939,10 +1991,10 @@ __global__ __launch_bounds__(1024) void block_sum4_atomic_kernel(const float4* _
     out[idx] = tot;
 }
 
-template <int SLOTS, int VAR, bool ANY>
+template <int SLOTS, int VAR, bool ANY, bool GRAD>
 hipError_t launch_score_k(const GridParams& g, const uint8_t* blob, int n, const float* gen, float* energy,
                           float* grad, float* atom_out, int n_cu, hipStream_t st) {
-    auto k = score_kernel<SLOTS, VAR, ANY>;
+    auto k = score_kernel<SLOTS, VAR, ANY, GRAD>;
     // resident blocks per CU, queried once per kernel (the query costs tens
     // of microseconds of host time, as much as a small call's kernel)
     static std::atomic<int> cached{0};
@@ -1964,12 +2016,15 @@ template <int VAR>
 hipError_t launch_score_v(const GridParams& g, const uint8_t* blob, int slots, int n,
                           const float* gen, float* energy, float* grad, float* atom_out, int n_cu,
                           hipStream_t st) {
-    const bool any = g.corners == nullptr;
-    if (slots == 1)
-        return any ? launch_score_k<1, VAR, true>(g, blob, n, gen, energy, grad, atom_out, n_cu, st)
-                   : launch_score_k<1, VAR, false>(g, blob, n, gen, energy, grad, atom_out, n_cu, st);
-    return any ? launch_score_k<2, VAR, true>(g, blob, n, gen, energy, grad, atom_out, n_cu, st)
-               : launch_score_k<2, VAR, false>(g, blob, n, gen, energy, grad, atom_out, n_cu, st);
+    // no gradient and no per-atom output asked for: the energy-only evaluation
+    const bool any = g.corners == nullptr, forces = grad || atom_out;
+    auto go = [&](auto launch) { return launch(g, blob, n, gen, energy, grad, atom_out, n_cu, st); };
+    if (slots == 1) {
+        if (forces) return any ? go(launch_score_k<1, VAR, true, true>) : go(launch_score_k<1, VAR, false, true>);
+        return any ? go(launch_score_k<1, VAR, true, false>) : go(launch_score_k<1, VAR, false, false>);
+    }
+    if (forces) return any ? go(launch_score_k<2, VAR, true, true>) : go(launch_score_k<2, VAR, false, true>);
+    return any ? go(launch_score_k<2, VAR, true, false>) : go(launch_score_k<2, VAR, false, false>);
 }
 
 template <int VAR>
@@ -2048,14 +2103,17 @@ hipError_t launch_score(const GridParams& g, const uint8_t* blob, int slots, int
 
 hipError_t launch_score_two(const GridParams& g, const uint8_t* blob, int n, const float* genotypes,
                             float* energy, float* grad, float* atom_out, int n_cu, hipStream_t stream) {
-    const bool any = g.corners == nullptr;
-    const void* k = any ? reinterpret_cast<const void*>(&score_kernel_two<true>)
-                        : reinterpret_cast<const void*>(&score_kernel_two<false>);
-    static std::atomic<int> cached[2];
-    int per_cu = cached[any ? 1 : 0].load(std::memory_order_relaxed);
+    const bool any = g.corners == nullptr, forces = grad || atom_out;
+    const void* k = forces ? (any ? reinterpret_cast<const void*>(&score_kernel_two<true, true>)
+                                  : reinterpret_cast<const void*>(&score_kernel_two<false, true>))
+                           : (any ? reinterpret_cast<const void*>(&score_kernel_two<true, false>)
+                                  : reinterpret_cast<const void*>(&score_kernel_two<false, false>));
+    static std::atomic<int> cached[4];
+    std::atomic<int>& slot = cached[2 * any + forces];
+    int per_cu = slot.load(std::memory_order_relaxed);
     if (per_cu <= 0) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64, 0) != hipSuccess || per_cu <= 0) per_cu = 2;
-        cached[any ? 1 : 0].store(per_cu, std::memory_order_relaxed);
+        slot.store(per_cu, std::memory_order_relaxed);
     }
     const long long pairs = ((long long)n + 1) / 2;
     const long long resident = (long long)per_cu * (n_cu > 0 ? n_cu : 256);
