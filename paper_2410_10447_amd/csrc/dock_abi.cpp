@@ -174,12 +174,15 @@ struct LsPlanBuf {
     docklaunch::DevItem* dev;
     int64_t* cost;
     int* fam;
+    int* batches;
     int* idx;
     uint8_t* table;
 };
 
 struct LsPart {
     int first, count, mode, variant;
+    int batches;                    // most pair batches of its ligands
+    bool corners;                   // every item reads corner-expanded maps
     int64_t units, block_units;
     double block_work, wave_work;   // shared launch: estimated wave-slot time of either phase
 };
@@ -280,6 +283,7 @@ int32_t ls_plan(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* 
                       ((int64_t)H->n_batches * 90 + (int64_t)d.slots * (150 + 20 * P.max_depth) + 500);
         const int f = two ? 4 : (tpi == 256 ? 0 : (tpi == 128 ? 1 : (d.slots == 1 ? 3 : 2)));
         fam[n_dev] = f;
+        buf.batches[n_dev] = H->n_batches;
         any_fam[f] = true;
         var_u = (var_u == -2 || var_u == var) ? var : -1;
         total += it.n;
@@ -322,7 +326,7 @@ int32_t ls_plan(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* 
                                                         docklaunch::kTwoPerWave};
             const int mode = unified ? docklaunch::kUnified
                                      : (merge_one_wave ? docklaunch::kSlotsAny : kModes[g]);
-            plan.part[plan.n_parts++] = {i, 0, mode, -1, 0, 0, 0.0, 0.0};
+            plan.part[plan.n_parts++] = {i, 0, mode, -1, 0, true, 0, 0, 0.0, 0.0};
             ub = 0;
         }
         tab[i] = dev[idx[i]];
@@ -344,6 +348,7 @@ int32_t ls_plan(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* 
             }
         }
         ++plan.part[plan.n_parts - 1].count;
+        plan.part[plan.n_parts - 1].batches = std::max(plan.part[plan.n_parts - 1].batches, buf.batches[idx[i]]);
     }
     // each launch runs the kernel specialised for its items' variant when
     // they share one (e.g. a tuning table that picks one per size bucket)
@@ -358,6 +363,7 @@ int32_t ls_plan(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* 
             corners = corners && tab[i].grid.corners != nullptr;
         }
         pt.variant = (v < 0 || !corners) ? -1 : v;
+        pt.corners = corners;
     }
     return ok();
 }
@@ -377,6 +383,25 @@ int shared_wave_blocks(const LsPart& pt, int grid) {
     if (total <= 0.0) return 0;
     const int w = (int)(kSharedWaveShare * grid * pt.wave_work / total);
     return std::max(0, std::min(grid, w));
+}
+
+// Waves per block when a part of one-wave items runs one individual per block
+// (same results), or 0 for a wave per individual. Sharing an individual costs
+// total work (the slot sums, 80 instructions more per wave) and pays while SIMDs
+// would idle: up to the individuals whose blocks are resident at once, 256 with
+// eight waves (48 atoms, per evaluation: 2.6 us against 4.6) and 512 with four
+// (3.6 against 4.9; 64 atoms 6.4 against 7.3). Past that a second round of
+// blocks costs more than waves of their own (600 individuals in two rounds 7.2
+// us against 5.0). For more than 64 atoms four waves gain nothing at 512 (20.3
+// us either way). A call of several launches side by side fills the GPU better
+// with one wave per individual.
+int coop_waves(const LsPlan& plan, const LsPart& pt, int n_cu) {
+    if (plan.n_parts != 1 || !pt.corners) return 0;
+    if (pt.mode != docklaunch::kSlots1 && pt.mode != docklaunch::kSlots2) return 0;
+    const bool keep = pt.batches <= docklaunch::kCoopKeep;
+    for (int waves = 8; waves >= (pt.mode == docklaunch::kSlots1 ? 4 : 8); waves /= 2)
+        if (pt.units <= (int64_t)docklaunch::coop_blocks_per_cu(pt.mode, waves, keep) * n_cu) return waves;
+    return 0;
 }
 
 // Launches the parts of a plan whose table is already on its way to `ws`
@@ -421,7 +446,10 @@ int32_t ls_launch(const LsPlan& plan, const LsPlanBuf& buf, void* ws, const dock
         p.rho = o->rho;
         p.eps = o->eps;
         hipStream_t s_k = (k == 0 || !side) ? stream : side->stream[k - 1];
-        launch_err = docklaunch::launch_ls(p, pt.mode, pt.variant, grid, s_k);
+        const int waves = coop_waves(plan, pt, n_cu);
+        launch_err = waves ? docklaunch::launch_ls_coop(p, pt.mode, waves, pt.batches <= docklaunch::kCoopKeep,
+                                                        (int)units, s_k)
+                           : docklaunch::launch_ls(p, pt.mode, pt.variant, grid, s_k);
         if (launch_err != hipSuccess) break;
     }
     if (side) {  // joined also after a failed launch
@@ -628,9 +656,9 @@ int32_t dock_local_search_batch(const dock_ls_item* items, int32_t n_items, cons
     if (n_items < 0 || (n_items > 0 && !items)) return fail(DOCK_EINVAL, "dock_local_search_batch: bad items");
     std::vector<docklaunch::DevItem> dev(std::max(n_items, 1));
     std::vector<int64_t> cost(std::max(n_items, 1));
-    std::vector<int> fam(std::max(n_items, 1)), idx(std::max(n_items, 1));
+    std::vector<int> fam(std::max(n_items, 1)), batches(std::max(n_items, 1)), idx(std::max(n_items, 1));
     std::vector<uint8_t> table(docklaunch::kWorkspaceHeader + (size_t)std::max(n_items, 1) * sizeof(docklaunch::DevItem));
-    LsPlanBuf buf{dev.data(), cost.data(), fam.data(), idx.data(), table.data()};
+    LsPlanBuf buf{dev.data(), cost.data(), fam.data(), batches.data(), idx.data(), table.data()};
     LsPlan plan;
     int32_t st = ls_plan(items, n_items, o, buf, plan);
     if (st != DOCK_OK || plan.n_parts == 0) return st;
@@ -652,9 +680,9 @@ int32_t dock_ls_launches(const dock_ls_item* items, int32_t n_items, const dock_
     if (n_items < 0 || (n_items > 0 && !items)) return fail(DOCK_EINVAL, "dock_ls_launches: bad items");
     std::vector<docklaunch::DevItem> dev(std::max(n_items, 1));
     std::vector<int64_t> cost(std::max(n_items, 1));
-    std::vector<int> fam(std::max(n_items, 1)), idx(std::max(n_items, 1));
+    std::vector<int> fam(std::max(n_items, 1)), batches(std::max(n_items, 1)), idx(std::max(n_items, 1));
     std::vector<uint8_t> table(docklaunch::kWorkspaceHeader + (size_t)std::max(n_items, 1) * sizeof(docklaunch::DevItem));
-    LsPlanBuf buf{dev.data(), cost.data(), fam.data(), idx.data(), table.data()};
+    LsPlanBuf buf{dev.data(), cost.data(), fam.data(), batches.data(), idx.data(), table.data()};
     LsPlan plan;
     const int32_t st = ls_plan(items, n_items, o, buf, plan);
     if (st != DOCK_OK) return st;
@@ -672,9 +700,9 @@ int32_t dock_local_search_batch_static(const dock_ls_item* items, int32_t n_item
                                      std::to_string(DOCK_STATIC_MAX_ITEMS) + ")");
     docklaunch::DevItem dev[DOCK_STATIC_MAX_ITEMS];
     int64_t cost[DOCK_STATIC_MAX_ITEMS];
-    int fam[DOCK_STATIC_MAX_ITEMS], idx[DOCK_STATIC_MAX_ITEMS];
+    int fam[DOCK_STATIC_MAX_ITEMS], batches[DOCK_STATIC_MAX_ITEMS], idx[DOCK_STATIC_MAX_ITEMS];
     alignas(16) uint8_t table[docklaunch::kWorkspaceHeader + DOCK_STATIC_MAX_ITEMS * sizeof(docklaunch::DevItem)];
-    LsPlanBuf buf{dev, cost, fam, idx, table};
+    LsPlanBuf buf{dev, cost, fam, batches, idx, table};
     LsPlan plan;
     int32_t st = ls_plan(items, n_items, o, buf, plan);
     if (st != DOCK_OK || plan.n_parts == 0) return st;

@@ -100,7 +100,9 @@ struct Header {
     int32_t off_chain;      // uint8[n_frag][kChainStride] enclosing torsions, innermost first
     int32_t off_plist;      // PairRec[n_batches][kBatch]
     int32_t slot_stride;    // accumulator stride, see slot_stride()
-    int32_t pad[14];
+    int32_t off_gather;     // uint16[ceil(n_batches / 8)][n_copies * slot_stride][8] gather
+                            // table (below)
+    int32_t pad[13];
 };
 static_assert(sizeof(Header) == 128, "header is 128 bytes");
 
@@ -112,6 +114,19 @@ struct PairRec {
     float c12, cm, ds;
 };
 static_assert(sizeof(PairRec) == 16, "pair record is 16 bytes");
+
+// Gather table: for the kernel that shares an individual's pairs among the
+// waves of a block, per accumulator slot the pairs that add to it, in batch
+// order. The pairs of kGatherRows consecutive batches lie in a buffer of rows
+// of kGatherRow bytes (64 pairs of 16 bytes, and a zero). An entry is a pair's
+// byte offset in its buffer, with kGatherMinus set when the slot is the pair's
+// first atom (which receives -w d); a slot's entries of one buffer are packed
+// at the front and filled up with kGatherNone (the first row's zero).
+constexpr int kGatherRows = 8;
+constexpr int kGatherRow = 16 * (kBatch + 1);
+constexpr uint16_t kGatherMinus = 0x8000;
+constexpr uint16_t kGatherNone = 16 * kBatch;
+static_assert(kGatherRows * kGatherRow <= kGatherMinus, "offsets fit 15 bits");
 
 struct Torsion {
     float p[4];      // axis point y0[a] (w unused)

@@ -20,6 +20,8 @@ hipError_t launch_score_two(const GridParams&, const uint8_t*, int, const float*
 }
 hipError_t launch_ls(const LsParams&, int, int, int, hipStream_t) { return hipErrorNoDevice; }
 int ls_blocks_per_cu(int, int) { return 0; }
+int coop_blocks_per_cu(int, int, bool) { return 0; }
+hipError_t launch_ls_coop(const LsParams&, int, int, bool, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_block_sum4(const float*, float*, int, int, int, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_expand_corners(const GridParams&, float*, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_sw(const GridParams&, const uint8_t*, int, int, const SwParams&, hipStream_t) {

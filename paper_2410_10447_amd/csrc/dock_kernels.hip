@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "dock.h"
@@ -85,6 +86,11 @@ __device__ __forceinline__ float readlane(float v, int l) {
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// Value of lane `l` mod 64 (the permute reads bits 2 to 7 of its byte address).
+__device__ __forceinline__ float lane_at(float v, uint32_t l) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)(l << 2), __builtin_bit_cast(int, v)));
+}
+
 // Ordering of LDS accesses between the lanes of one wave, where one wave is
 // everything that shares the data: a wave's LDS instructions execute in
 // program order, so it only has to keep the compiler from moving LDS
@@ -104,6 +110,10 @@ __device__ __forceinline__ void lds_sync() {
     if constexpr (WAVES == 1) wave_sync();
     else __syncthreads();
 }
+
+// Block barrier that orders LDS accesses only: __syncthreads also waits for the
+// wave's global loads, which the shared evaluation keeps in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Wave-uniform value: lets the compiler keep it (and what is derived from it,
 // such as loop bounds and addresses) in scalar registers.
@@ -300,6 +310,21 @@ __device__ __forceinline__ float sum1(float v) {
 // Ligand data held by a wave.
 // ---------------------------------------------------------------------------
 
+// Torsion transforms (3x4, row-major) and pair-force accumulators of one
+// individual share memory: transform k lives until the atom positions are
+// written, the accumulators from then on. The identity (transform kMaxTors)
+// lies past the accumulators, so that it is written once per ligand.
+template <int SLOTS>
+struct __align__(16) TorsionAcc {
+    static constexpr int kFirst = SLOTS > 3 * kMaxTors ? SLOTS - 3 * kMaxTors : 0;
+    float4 acc[kFirst + 3 * kMaxTors];
+    float4 identity[3];
+    __device__ __forceinline__ float4* transforms() { return acc + kFirst; }
+    __device__ __forceinline__ void write_identity(int row) {
+        identity[row] = make_float4(row == 0 ? 1.f : 0.f, row == 1 ? 1.f : 0.f, row == 2 ? 1.f : 0.f, 0.f);
+    }
+};
+
 // LDS of one individual. Sized per layout: SLOTS atoms per lane and WAVES
 // waves per individual (a wave of the two- and four-wave layouts owns 64
 // atom positions, of which past the ligand's last atom none is used, and its
@@ -312,15 +337,9 @@ struct __align__(16) Smem {
         (SLOTS == 1 && WAVES == 1) ? dockblob::kMaxSlotsSmall : dockblob::kMaxSlots * WAVES;
     float4 dyn[kAtoms];             // x, y, z relative to t, and sqrt(kElec) q (depth-first
                                     // order); zero past the last atom
-    union {
-        float tk[kMaxTors + 1][12]; // torsion transforms, 3x4 row-major, and the identity
-                                    // (index kMaxTors); live until the atom positions are
-                                    // written
-        float4 acc[kSlots];         // pair-force accumulators, slot = (range * C + copy) *
-                                    // stride + atom, one range per wave
-    } u;
-    float4 tor[kMaxTors][2];        // torsion k: axis point p and packed positions
-                                    // (a | b << 8 | first << 16 | end << 24), unit axis u
+    TorsionAcc<kSlots> u;           // accumulator slot = (range * C + copy) * stride + atom, one
+                                    // range per wave
+    float4 tor[kMaxTors][2];        // torsion k: axis point p, unit axis u
     uint32_t chain[kMaxFrag][kChain / 4];  // per fragment: enclosing torsions, innermost
                                            // first, 4 per word, padded with the identity
     // several waves per individual: each wave's prefix sums of (g, x cross g)
@@ -345,15 +364,26 @@ struct Lig {
     int cls[SLOTS];
     int frag[SLOTS];
     int orig[SLOTS];                // original atom index
+    // the torsion of this lane's gene (gene 7 + k is torsion k's angle): depth-first
+    // positions of the bond atoms a, b, and of the atoms before the first and
+    // at the end of the moving range, a | b << 8 | (first - 1) << 16 | (end - 1) << 24
+    uint32_t torsion;
 };
+constexpr int kFirstTorsion = 7;    // its gene
 
-template <int SLOTS, int WAVES = 1>
-__device__ void load_ligand(const uint8_t* __restrict__ blob, Smem<SLOTS, WAVES>& sm, Lig<SLOTS>& L,
-                            bool fill_lds = true) {
-    if (fill_lds) lds_sync<WAVES>();  // previous users of the LDS tables are done
+// The packed torsion word of Lig; lanes without a torsion get harmless positions.
+__device__ __forceinline__ uint32_t torsion_word(const uint8_t* blob, int T, int k) {
+    if (k < 0 || k >= T) return 0;
+    const Torsion& t = reinterpret_cast<const Torsion*>(blob + reinterpret_cast<const Header*>(blob)->off_tors)[k];
+    return (uint32_t)t.a_pos | (uint32_t)t.b_pos << 8 | (uint32_t)(t.first - 1) << 16 | (uint32_t)(t.end - 1) << 24;
+}
+
+// Header fields and this wave's atoms (`wv`: which 64 x SLOTS of them).
+template <int SLOTS>
+__device__ __forceinline__ void load_atoms(const uint8_t* __restrict__ blob, int wv, Lig<SLOTS>& L) {
     const Header* h = reinterpret_cast<const Header*>(blob);
     const int lane = lane_id();
-    L.wv = WAVES == 1 ? 0 : uniform((int)threadIdx.x >> 6);
+    L.wv = wv;
     L.N = uniform(h->n_atoms);
     L.T = uniform(h->n_torsions);
     L.NF = uniform(h->n_frag);
@@ -384,18 +414,33 @@ __device__ void load_ligand(const uint8_t* __restrict__ blob, Smem<SLOTS, WAVES>
         L.frag[s] = ok ? ii.y : 0;
         L.orig[s] = ii.z;
     }
+    L.torsion = torsion_word(blob, L.T, lane - kFirstTorsion);
+}
+
+// The LDS tables of a ligand: torsions and the identity (by the threads of the first wave) and
+// fragment chains (by `threads` threads).
+template <class SM>
+__device__ __forceinline__ void fill_tables(const uint8_t* __restrict__ blob, SM& sm, int T, int NF, int thread,
+                                            int threads) {
+    const Header* h = reinterpret_cast<const Header*>(blob);
     const Torsion* tr = reinterpret_cast<const Torsion*>(blob + h->off_tors);
-    if (fill_lds && L.wv == 0 && lane < L.T) {
-        const Torsion t = tr[lane];
-        const int pk = t.a_pos | (t.b_pos << 8) | (t.first << 16) | (t.end << 24);
-        sm.tor[lane][0] = make_float4(t.p[0], t.p[1], t.p[2], __int_as_float(pk));
-        sm.tor[lane][1] = make_float4(t.u[0], t.u[1], t.u[2], 0.f);
+    if (thread < T) {
+        const Torsion t = tr[thread];
+        sm.tor[thread][0] = make_float4(t.p[0], t.p[1], t.p[2], 0.f);
+        sm.tor[thread][1] = make_float4(t.u[0], t.u[1], t.u[2], 0.f);
     }
+    if (thread < 3) sm.u.write_identity(thread);
     const uint32_t* ch = reinterpret_cast<const uint32_t*>(blob + h->off_chain);
-    const int n_chain_words = L.NF * (kChain / 4);
     uint32_t* dst = &sm.chain[0][0];
-    if (fill_lds)
-        for (int i = WAVES == 1 ? lane : (int)threadIdx.x; i < n_chain_words; i += kWave * WAVES) dst[i] = ch[i];
+    for (int i = thread; i < NF * (kChain / 4); i += threads) dst[i] = ch[i];
+}
+
+template <int SLOTS, int WAVES = 1>
+__device__ void load_ligand(const uint8_t* __restrict__ blob, Smem<SLOTS, WAVES>& sm, Lig<SLOTS>& L,
+                            bool fill_lds = true) {
+    if (fill_lds) lds_sync<WAVES>();  // previous users of the LDS tables are done
+    load_atoms<SLOTS>(blob, WAVES == 1 ? 0 : uniform((int)threadIdx.x >> 6), L);
+    if (fill_lds) fill_tables(blob, sm, L.T, L.NF, WAVES == 1 ? lane_id() : (int)threadIdx.x, kWave * WAVES);
     lds_sync<WAVES>();
 }
 
@@ -581,15 +626,14 @@ __device__ __forceinline__ void grid_term(const GridParams& G, const GridTaps& t
 // (a, b, m) = (1, -2, 6), 12-10 hydrogen bond (5, -6, 10); r dE/dr is
 // -12 A / r^12 - m B / r^m. `live` masks pairs that are not kept (e = w = 0)
 // and `slope` masks the slope where r^2 is clamped (selects, so a masked
-// NaN or infinity gives 0 too). XFIRST: the order in which the squares of the
+// NaN or infinity gives 0 too). xfirst: the order in which the squares of the
 // separation are added, dy^2 before dx^2 or the other way round; the callers
 // fix it per pipeline step, since a different order rounds differently.
 // ---------------------------------------------------------------------------
 
-template <bool XFIRST>
-__device__ __forceinline__ void pair_term(float dx, float dy, float dz, float A, float B, bool hb,
+__device__ __forceinline__ void pair_term(bool xfirst, float dx, float dy, float dz, float A, float B, bool hb,
                                           float qq, float ds, bool live, float& e, float& w) {
-    const float r2raw = fmaf(dz, dz, XFIRST ? fmaf(dy, dy, dx * dx) : fmaf(dx, dx, dy * dy));
+    const float r2raw = fmaf(dz, dz, xfirst ? fmaf(dy, dy, dx * dx) : fmaf(dx, dx, dy * dy));
     const bool slope = live && (r2raw >= kR2Min);
     const float r2 = fmaxf(r2raw, kR2Min);
     const float rinv = __builtin_amdgcn_rsqf(r2);
@@ -640,8 +684,7 @@ struct IntC { static constexpr int value = V; };
 
 // Unused lanes (A = -0.0f) carry two slots no pair of their batch uses and
 // get zero energy and force, so every lane updates its slots.
-template <bool XFIRST = false>
-__device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj) {
+__device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj, bool xfirst = false) {
     PairForce o;
     const uint32_t rec = pr.x;
     const bool valid = pr.y != dockblob::kPadC12;
@@ -649,7 +692,7 @@ __device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj) 
     const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
     const float qq = pi.w * pj.w;           // charges pre-scaled by sqrt(kElec)
     float e, w;
-    pair_term<XFIRST>(dx, dy, dz, __uint_as_float(pr.y), __uint_as_float(pr.z), hb, qq,
+    pair_term(xfirst, dx, dy, dz, __uint_as_float(pr.y), __uint_as_float(pr.z), hb, qq,
               __uint_as_float(pr.w), valid, e, w);
     o.e = e;
     o.w = w;
@@ -774,6 +817,161 @@ __device__ __forceinline__ float adadelta(float x, float gr, float rho, float ep
     return fmaf(rate, gr, x);
 }
 
+// Atom positions of the individual whose genes this wave holds: relative to
+// the translation genes `tv`, in registers (x) and in the LDS position table.
+template <int SLOTS, int WAVES, int LEVELS = 2, class SM>
+__device__ __forceinline__ void pose(SM& sm, const Lig<SLOTS>& L, float gene, Rot& Rq, float tv[3],
+                                     float x[SLOTS][3]) {
+    const int lane = lane_id();
+    const bool lead = WAVES == 1 || L.wv == 0;  // the wave that writes shared tables
+    // rigid-body genes (uniform)
+    const float tx = readlane(gene, 0), ty = readlane(gene, 1), tz = readlane(gene, 2);
+    const float qw0 = readlane(gene, 3), qx0 = readlane(gene, 4), qy0 = readlane(gene, 5),
+                qz0 = readlane(gene, 6);
+    Rq = rotation(qw0, qx0, qy0, qz0);
+
+    // torsion transforms: T_k(y) = R_k (y - p) + p, about the reference axis, by
+    // the lane that holds the angle
+    const int k = lane - kFirstTorsion;
+    if (lead && k >= 0 && k < L.T) {
+        torsion_transform(gene, sm.tor[k][0], sm.tor[k][1], sm.u.transforms() + 3 * k);
+    }
+    lds_sync<WAVES>();
+    // atom positions relative to the rotation centre: the torsions enclosing
+    // the atom's fragment, innermost first (each about its reference axis,
+    // which no inner torsion moves), then the rotation Rq. The translation t
+    // is added only where world coordinates are needed (the grid term): pair
+    // separations, torques and torsion axes are translation invariant and
+    // keep the precision of the small local coordinates.
+    tv[0] = tx; tv[1] = ty; tv[2] = tz;
+    static_assert(LEVELS == 2 || LEVELS == 4, "a chain word holds four levels");
+    const int n_trips = (L.max_depth + LEVELS - 1) / LEVELS;   // LDS round trips, LEVELS levels each
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int a = lane + kWave * (s + L.wv);
+        float y0 = L.y0[s][0], y1 = L.y0[s][1], y2 = L.y0[s][2];
+        // one word of torsion indices per four levels; levels past the atom's
+        // depth apply the identity, so every lane takes the same (uniform)
+        // number of trips
+        const uint32_t* row = sm.chain[L.frag[s]];
+        for (int d = 0; d < n_trips; ++d) {
+            const uint32_t w = LEVELS == 4 ? row[d] : row[d >> 1] >> (16 * (d & 1));
+            float4 T[LEVELS][3];
+#pragma unroll
+            for (int q = 0; q < LEVELS; ++q) {
+                const unsigned k = (w >> (8 * q)) & 255u;
+                const float4* t = reinterpret_cast<const float4*>(__builtin_assume_aligned(
+                    reinterpret_cast<const char*>(sm.u.transforms()) + __umul24(k, 48u), 16));
+                T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
+            }
+#pragma unroll
+            for (int q = 0; q < LEVELS; ++q) apply_transform(T[q], y0, y1, y2);
+        }
+        rotate(Rq, y0, y1, y2, x[s]);
+        sm.dyn[a] = make_float4(x[s][0], x[s][1], x[s][2], kSqrtElec * L.chg[s][1]);
+    }
+    lds_sync<WAVES>();
+}
+
+// Sum of an atom's `n` accumulator copies, `stride` slots apart, in copy order;
+// four reads in flight at a time.
+__device__ __forceinline__ void sum_copies(const float4* acc, int n, int stride, float g[3]) {
+    g[0] = g[1] = g[2] = 0.f;
+    int c = 0;
+    for (; c + 4 <= n; c += 4, acc += 4 * stride) {
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = acc[k * stride];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { g[0] += v[k].x; g[1] += v[k].y; g[2] += v[k].z; }
+    }
+    for (; c < n; ++c, acc += stride) {
+        const float4 v = *acc;
+        g[0] += v.x; g[1] += v.y; g[2] += v.z;
+    }
+}
+
+// Energy and this lane's gradient component from the per-atom gradients `g`
+// and the lane energies; `sum` is the block sum of 4-vectors.
+template <int SLOTS, int WAVES, class SM, class SUM>
+__device__ __forceinline__ float finish(SM& sm, const Lig<SLOTS>& L, const Rot& Rq, const float x[SLOTS][3],
+                                        const float g[SLOTS][3], float e_lane, SUM&& sum, float& grad) {
+    const int lane = lane_id();
+    // this lane's torsion: positions of its bond atoms, read ahead of the sums
+    const float4 bond_a = sm.dyn[L.torsion & 255], bond_b = sm.dyn[(L.torsion >> 8) & 255];
+    // block sum of {E, gx, gy, gz}: the paper's reduction, in the chosen variant
+    float4 eg = make_float4(e_lane, g[0][0], g[0][1], g[0][2]);
+    if constexpr (SLOTS == 2) { eg.y += g[1][0]; eg.z += g[1][1]; eg.w += g[1][2]; }
+    float4 EG = sum(eg);
+
+    // torsion torques: prefix sums of (g, x cross g) in depth-first order;
+    // the last lane's x cross g sums give the torque about t (FP32 always)
+    float P[SLOTS][6];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        P[s][0] = g[s][0]; P[s][1] = g[s][1]; P[s][2] = g[s][2];
+        P[s][3] = fmaf(x[s][1], g[s][2], -(x[s][2] * g[s][1]));
+        P[s][4] = fmaf(x[s][2], g[s][0], -(x[s][0] * g[s][2]));
+        P[s][5] = fmaf(x[s][0], g[s][1], -(x[s][1] * g[s][0]));
+    }
+    wave_scan6(P[0]);
+    if constexpr (SLOTS == 2) {
+        wave_scan6(P[1]);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) P[1][c] += readlane(P[0][c], 63);
+    }
+    float4 TQ = make_float4(readlane(P[SLOTS - 1][3], 63), readlane(P[SLOTS - 1][4], 63),
+                            readlane(P[SLOTS - 1][5], 63), 0.f);
+    if constexpr (WAVES > 1) {
+        // the waves' partials and prefix sums meet in LDS; every wave then
+        // holds the same totals (added in wave order) and steps identically
+        const int a = lane + kWave * L.wv;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sm.pre[c][a] = P[0][c];
+        if (lane == 0) sm.xchg[L.wv][0] = EG;
+        lds_sync<WAVES>();
+        EG = sm.xchg[0][0];
+        TQ = make_float4(sm.pre[3][kWave - 1], sm.pre[4][kWave - 1], sm.pre[5][kWave - 1], 0.f);
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const float4 ew = sm.xchg[w][0];
+            EG = make_float4(EG.x + ew.x, EG.y + ew.y, EG.z + ew.z, EG.w + ew.w);
+            TQ = make_float4(TQ.x + sm.pre[3][(w + 1) * kWave - 1], TQ.y + sm.pre[4][(w + 1) * kWave - 1],
+                             TQ.z + sm.pre[5][(w + 1) * kWave - 1], 0.f);
+        }
+    }
+    // sums over the atoms this lane's torsion moves: differences of the prefix
+    // sums at the end of the range and before its start
+    float S[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        if constexpr (WAVES > 1) {
+            // global prefix: a wave's local prefix plus the totals of the
+            // waves before it (added in wave order)
+            const int hi = L.torsion >> 24, lo = (L.torsion >> 16) & 255;
+            const float bh = sm.pre[c][hi], bl = sm.pre[c][lo];
+            float ph = bh, pl = bl, off = 0.f;
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) {
+                off = w == 1 ? sm.pre[c][kWave - 1] : off + sm.pre[c][w * kWave - 1];
+                ph = hi >= w * kWave ? bh + off : ph;
+                pl = lo >= w * kWave ? bl + off : pl;
+            }
+            S[c] = ph - pl;
+        } else {
+            float ph = lane_at(P[0][c], L.torsion >> 24), pl = lane_at(P[0][c], L.torsion >> 16);
+            if constexpr (SLOTS == 2) {
+                const float ph1 = lane_at(P[1][c], L.torsion >> 24), pl1 = lane_at(P[1][c], L.torsion >> 16);
+                ph = (L.torsion >> 24) >= kWave ? ph1 : ph;
+                pl = ((L.torsion >> 16) & 255) >= kWave ? pl1 : pl;
+            }
+            S[c] = ph - pl;
+        }
+    }
+    grad = gene_gradient(lane, EG, TQ, Rq, torsion_gradient(S, bond_a, bond_b));
+    return EG.x;
+}
+
 // ---------------------------------------------------------------------------
 // One evaluation of E and dE/dgenotype for the individual held by this wave.
 // `gene` is gene `lane` (lanes >= G ignored); returns E (uniform) and writes
@@ -784,58 +982,9 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                           float& grad, float* atom_out) {
     const int lane = lane_id();
     const int N = L.N;
-    const bool lead = WAVES == 1 || L.wv == 0;  // the wave that writes shared tables
-    // rigid-body genes (uniform)
-    const float tx = readlane(gene, 0), ty = readlane(gene, 1), tz = readlane(gene, 2);
-    const float qw0 = readlane(gene, 3), qx0 = readlane(gene, 4), qy0 = readlane(gene, 5),
-                qz0 = readlane(gene, 6);
-    const Rot Rq = rotation(qw0, qx0, qy0, qz0);
-
-    // torsion transforms: T_k(y) = R_k (y - p) + p, about the reference axis
-    const float psi = __shfl(gene, (7 + lane) & 63);
-    if (lead && lane < L.T) {
-        torsion_transform(psi, sm.tor[lane][0], sm.tor[lane][1], reinterpret_cast<float4*>(sm.u.tk[lane]));
-    } else if (lead && lane == kMaxTors) {
-        float4* o = reinterpret_cast<float4*>(sm.u.tk[kMaxTors]);
-        o[0] = make_float4(1.f, 0.f, 0.f, 0.f);
-        o[1] = make_float4(0.f, 1.f, 0.f, 0.f);
-        o[2] = make_float4(0.f, 0.f, 1.f, 0.f);
-    }
-    lds_sync<WAVES>();
-    // atom positions relative to the rotation centre: the torsions enclosing
-    // the atom's fragment, innermost first (each about its reference axis,
-    // which no inner torsion moves), then the rotation Rq. The translation t
-    // is added only where world coordinates are needed (the grid term): pair
-    // separations, torques and torsion axes are translation invariant and
-    // keep the precision of the small local coordinates.
-    const float tv[3] = {tx, ty, tz};
-    const int n_duos = (L.max_depth + 1) >> 1;   // levels, two per LDS round trip
-    float x[SLOTS][3];
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        const int a = lane + kWave * (s + L.wv);
-        float y0 = L.y0[s][0], y1 = L.y0[s][1], y2 = L.y0[s][2];
-        // one word of torsion indices per four levels; two levels per LDS
-        // round trip; levels past the atom's depth apply the identity, so
-        // every lane takes the same (uniform) number of level pairs
-        const uint32_t* row = sm.chain[L.frag[s]];
-        for (int d = 0; d < n_duos; ++d) {
-            const uint32_t w = row[d >> 1] >> (16 * (d & 1));
-            float4 T[2][3];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const unsigned k = (w >> (8 * q)) & 255u;
-                const float4* t = reinterpret_cast<const float4*>(__builtin_assume_aligned(
-                    reinterpret_cast<const char*>(sm.u.tk) + __umul24(k, 48u), 16));
-                T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) apply_transform(T[q], y0, y1, y2);
-        }
-        rotate(Rq, y0, y1, y2, x[s]);
-        sm.dyn[a] = make_float4(x[s][0], x[s][1], x[s][2], kSqrtElec * L.chg[s][1]);
-    }
-    lds_sync<WAVES>();
+    Rot Rq;
+    float tv[3], x[SLOTS][3];
+    pose<SLOTS, WAVES>(sm, L, gene, Rq, tv, x);
 
     float g[SLOTS][3];
     float e_lane = 0.f;
@@ -884,7 +1033,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 __builtin_amdgcn_sched_barrier(0);   // keep the position reads at the step's start
                 constexpr bool last = decltype(load)::value == 0;
                 constexpr bool xfirst = (TRIAL && r == 0) || (last && r == 2);
-                e_lane += pair_force<xfirst>(R[r], Pi[c], Pj[c]).e;
+                e_lane += pair_force(R[r], Pi[c], Pj[c], xfirst).e;
                 if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
                 __builtin_amdgcn_sched_barrier(0);
                 ++k;
@@ -978,7 +1127,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 Pj[c] = pos_j(rf.x);
                 if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
                 __builtin_amdgcn_sched_barrier(0);   // keep the loads at the step's start
-                F[n] = pair_force<r == 1 && decltype(load)::value == 0>(R[(r + 1) & 3], Pi[n], Pj[n]);
+                F[n] = pair_force(R[(r + 1) & 3], Pi[n], Pj[n], r == 1 && decltype(load)::value == 0);
                 store_force(accw, F[c], Ai[c], Aj[c]);
                 e_lane += F[c].e;
                 Ai[n] = *slot(accw, F[n].si);
@@ -1022,14 +1171,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         for (int s = 0; s < SLOTS; ++s) {
             const int a = lane + kWave * (s + L.wv);
             g[s][0] = g[s][1] = g[s][2] = 0.f;
-            if (a < N) {
-                for (int c = 0; c < L.n_copies * WAVES; ++c) {
-                    const float4 v = sm.u.acc[c * L.stride + a];
-                    g[s][0] += v.x;
-                    g[s][1] += v.y;
-                    g[s][2] += v.z;
-                }
-            }
+            if (a < N) sum_copies(sm.u.acc + a, L.n_copies * WAVES, L.stride, g[s]);
         }
     }
     // grid term, from the corner values loaded before the pair phase
@@ -1053,86 +1195,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         return sum1<VAR>(e_lane);
     }
 
-    // block sum of {E, gx, gy, gz}: the paper's reduction, in the chosen variant
-    float4 eg = make_float4(e_lane, g[0][0], g[0][1], g[0][2]);
-    if constexpr (SLOTS == 2) { eg.y += g[1][0]; eg.z += g[1][1]; eg.w += g[1][2]; }
-    float4 EG = sum4<VAR>(eg);
-
-    // torsion torques: prefix sums of (g, x cross g) in depth-first order;
-    // the last lane's x cross g sums give the torque about t (FP32 always)
-    float P[SLOTS][6];
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        P[s][0] = g[s][0]; P[s][1] = g[s][1]; P[s][2] = g[s][2];
-        P[s][3] = fmaf(x[s][1], g[s][2], -(x[s][2] * g[s][1]));
-        P[s][4] = fmaf(x[s][2], g[s][0], -(x[s][0] * g[s][2]));
-        P[s][5] = fmaf(x[s][0], g[s][1], -(x[s][1] * g[s][0]));
-    }
-    wave_scan6(P[0]);
-    if constexpr (SLOTS == 2) {
-        wave_scan6(P[1]);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) P[1][c] += readlane(P[0][c], 63);
-    }
-    float4 TQ = make_float4(readlane(P[SLOTS - 1][3], 63), readlane(P[SLOTS - 1][4], 63),
-                            readlane(P[SLOTS - 1][5], 63), 0.f);
-    if constexpr (WAVES > 1) {
-        // the waves' partials and prefix sums meet in LDS; every wave then
-        // holds the same totals (added in wave order) and steps identically
-        const int a = lane + kWave * L.wv;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) sm.pre[c][a] = P[0][c];
-        if (lane == 0) sm.xchg[L.wv][0] = EG;
-        lds_sync<WAVES>();
-        EG = sm.xchg[0][0];
-        TQ = make_float4(sm.pre[3][kWave - 1], sm.pre[4][kWave - 1], sm.pre[5][kWave - 1], 0.f);
-#pragma unroll
-        for (int w = 1; w < WAVES; ++w) {
-            const float4 ew = sm.xchg[w][0];
-            EG = make_float4(EG.x + ew.x, EG.y + ew.y, EG.z + ew.z, EG.w + ew.w);
-            TQ = make_float4(TQ.x + sm.pre[3][(w + 1) * kWave - 1], TQ.y + sm.pre[4][(w + 1) * kWave - 1],
-                             TQ.z + sm.pre[5][(w + 1) * kWave - 1], 0.f);
-        }
-    }
-    float gpsi = 0.f;
-    {
-        // torsion `lane`: bond atoms a, b and its moving range [first, end)
-        // in depth-first positions; lanes without a torsion read a harmless
-        // default (a = b = 0, empty range at 1)
-        const int pk = lane < L.T ? __float_as_int(sm.tor[lane & (kMaxTors - 1)][0].w) : (1 << 16) | (1 << 24);
-        const int t_apos = pk & 255, t_bpos = (pk >> 8) & 255;
-        const int hi = ((pk >> 24) & 255) - 1, lo = ((pk >> 16) & 255) - 1;
-        float S[6];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            if constexpr (WAVES > 1) {
-                // global prefix: a wave's local prefix plus the totals of the
-                // waves before it (added in wave order)
-                const float bh = sm.pre[c][hi], bl = sm.pre[c][lo];
-                float ph = bh, pl = bl, off = 0.f;
-#pragma unroll
-                for (int w = 1; w < WAVES; ++w) {
-                    off = w == 1 ? sm.pre[c][kWave - 1] : off + sm.pre[c][w * kWave - 1];
-                    ph = hi >= w * kWave ? bh + off : ph;
-                    pl = lo >= w * kWave ? bl + off : pl;
-                }
-                S[c] = ph - pl;
-            } else {
-                float ph = __shfl(P[0][c], hi & 63);
-                float pl = __shfl(P[0][c], lo & 63);
-                if constexpr (SLOTS == 2) {
-                    const float ph1 = __shfl(P[1][c], hi & 63);
-                    const float pl1 = __shfl(P[1][c], lo & 63);
-                    ph = hi >= kWave ? ph1 : ph;
-                    pl = lo >= kWave ? pl1 : pl;
-                }
-                S[c] = ph - pl;
-            }
-        }
-        const float gt = torsion_gradient(S, sm.dyn[t_apos], sm.dyn[t_bpos]);
-        gpsi = lane < L.T ? gt : 0.f;
-    }
-    grad = gene_gradient(lane, EG, TQ, Rq, __shfl(gpsi, (lane - 7) & 63));
+    const float E = finish<SLOTS, WAVES>(sm, L, Rq, x, g, e_lane, [](float4 v) { return sum4<VAR>(v); }, grad);
     if (atom_out) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
@@ -1145,7 +1208,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             }
         }
     }
-    return EG.x;
+    return E;
 }
 
 // ---------------------------------------------------------------------------
@@ -1260,15 +1323,14 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void sw_kernel(GridParams
     }
 }
 
-template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true>
-__device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L,
-                                 int iterations, float rho, float eps, bool final_eval) {
-    // with several waves per individual every wave holds the genotype and
-    // takes the same steps on the same totals; the first wave writes the
-    // results
+// ADADELTA search of individual `ind` by one wave, gene `lane`; `eval` returns
+// E and the gradient component at the current point. With several waves per
+// individual that hold the genotype all take the same steps on the same
+// totals, and the `writer` writes the results.
+template <class EVAL>
+__device__ __forceinline__ void search(const DevItem& it, int ind, int G, int iterations, float rho, float eps,
+                                       bool final_eval, bool writer, EVAL&& eval) {
     const int lane = lane_id();
-    const bool writer = WAVES == 1 || L.wv == 0;
-    const int G = L.G;
     const bool act = lane < G;
     const size_t o = (size_t)ind * G + lane;
     float x = act ? it.genotype[o] : 0.f;
@@ -1278,12 +1340,15 @@ __device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>&
     float bestE = it.best_energy[ind];
     float lastE = it.energy[ind];
     float lastG = 0.f;
-    for (int iter = 0; iter < iterations; ++iter) {
+    // the final evaluation, if asked for, is one more pass without a step
+    const int passes = iterations + (final_eval ? 1 : 0);
+    for (int pass = 0; pass < passes; ++pass) {
         float gr;
-        const float E = evaluate<SLOTS, VAR, WAVES, ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
+        const float E = eval(x, gr);
         lastE = E;
         lastG = gr;
         if (E < bestE) { bestE = E; bx = x; }
+        if (pass == iterations) break;
         gr = act ? gr : 0.f;
         float xn = adadelta(x, gr, rho, eps, ag, ad);
         const bool isq = lane >= 3 && lane < 7;
@@ -1292,13 +1357,6 @@ __device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>&
         const float nq2 = (row_lane<3>(q2) + row_lane<4>(q2)) + (row_lane<5>(q2) + row_lane<6>(q2));
         if (isq) xn = (nq2 >= 1e-12f) ? xn * __builtin_amdgcn_rsqf(nq2) : x;
         x = act ? xn : 0.f;
-    }
-    if (final_eval) {
-        float gr;
-        const float E = evaluate<SLOTS, VAR, WAVES, ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
-        lastE = E;
-        lastG = gr;
-        if (E < bestE) { bestE = E; bx = x; }
     }
     if (!writer) return;
     if (act && it.grad && (iterations > 0 || final_eval)) it.grad[o] = lastG;
@@ -1313,6 +1371,14 @@ __device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>&
         it.energy[ind] = lastE;
         it.iters_done[ind] += iterations;
     }
+}
+
+template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true>
+__device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L,
+                                 int iterations, float rho, float eps, bool final_eval) {
+    search(it, ind, L.G, iterations, rho, eps, final_eval, WAVES == 1 || L.wv == 0, [&](float x, float& gr) {
+        return evaluate<SLOTS, VAR, WAVES, ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
+    });
 }
 
 template <int SLOTS, int WAVES>
@@ -1436,6 +1502,333 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3
 }
 
 // ---------------------------------------------------------------------------
+// One individual per block, for populations too small to fill the GPU with a
+// wave each: the waves of a block share the pair terms of one individual and
+// give the result of the one-wave evaluation bit for bit. A lone wave needs
+// some 11,000 cycles per evaluation (48 atoms, 886 pairs), 6,400 of them in the
+// pair batches, whose accumulator slots chain one batch to the next, and the
+// rest of the GPU idles.
+//
+// Wave role 0 leads: it holds the genotype and does what the one-wave kernel
+// does outside the pair terms. Per evaluation the waves meet three times:
+//   positions written (role 0) | pair terms, batches dealt out to the waves,
+//   each pair's (d, w) and energy left in LDS | accumulator slots summed by
+//   all threads, a thread per slot, from the pairs that the ligand's gather
+//   table names in batch order (the order the one-wave kernel adds them in),
+//   the lane energies and the grid term by the last two roles | totals,
+//   genotype gradient and step (role 0).
+// More batches than a buffer holds go in chunks through two buffers in turn:
+// while one is summed the other is filled, one barrier per chunk.
+//
+// Bound by the leader's serial part, 3,200 of 5,800 cycles. Per evaluation at
+// 256 individuals, one wave against this: 24 atoms 2.6 and 2.4 us, 48 atoms 4.6
+// and 2.6, 64 atoms (28 batches) 6.9 and 4.2, 112 atoms (90 batches) 19.1 and
+// 10.0; with four waves at 512 individuals 48 atoms 4.9 and 3.6, 64 atoms 7.3
+// and 6.4.
+// ---------------------------------------------------------------------------
+constexpr int kPairRow = dockblob::kGatherRow / 16;   // float4s per batch: 64 pairs and a zero
+constexpr int kCoopRows = docklaunch::kCoopKeep;        // batches a buffer holds
+
+template <int SLOTS>
+struct __align__(16) SmemC {
+    static constexpr int kSlots = SLOTS == 1 ? dockblob::kMaxSlotsSmall : dockblob::kMaxSlots;
+    float4 dyn[kWave * SLOTS];                  // as in Smem
+    TorsionAcc<0> u;                            // the transforms alone
+    float4 tor[kMaxTors][2];
+    uint32_t chain[kMaxFrag][kChain / 4];
+    float4 acc[kSlots];                         // summed accumulator slots
+    float4 grid[kWave * SLOTS];                 // per atom: grid energy and gradient
+    float esum[kWave];                          // lane energies of the pairs
+    float t[4];                                 // translation genes
+    int unit, go;                               // work unit; another evaluation follows
+};
+
+// What a wave needs of the shared pair terms.
+struct CoopPairs {
+    const u32x4* table;     // gather table: [octet of batches][slot], eight entries each
+    float4* pair;           // one or two buffers of kCoopRows x kPairRow
+    float* energy;          // and of kCoopRows x 64
+    int nslot, role;
+};
+
+// Two unused gather table entries.
+constexpr uint32_t kGatherPad = dockblob::kGatherNone | (uint32_t)dockblob::kGatherNone << 16;
+
+// A wave's share of one chunk of batches, in registers: its records, and the
+// gather table entries of its threads' accumulator slots.
+template <int SLOTS, int W>
+struct CoopShare {
+    static constexpr int kOctets = kCoopRows / dockblob::kGatherRows;
+    static constexpr int kMine = kCoopRows / W;                                                      // batches
+    static constexpr int kOwn = (SmemC<SLOTS>::kSlots + W * kWave - 1) / (W * kWave);              // slots
+    static_assert(kCoopRows % W == 0 && kCoopRows % dockblob::kGatherRows == 0, "whole octets, dealt out evenly");
+    u32x4 rec[kMine];
+    u32x4 tab[kOwn][kOctets];
+    int words[kOwn][kOctets];           // of the entries (two to a word), how many any lane needs
+
+    // `chunk` exists; indices past the last batch or slot are clamped, so that
+    // the loads need no branch
+    __device__ __forceinline__ void load(const Lig<SLOTS>& L, const CoopPairs& c, int chunk) {
+        const auto at = gmem(L.plist) + lane_id();
+#pragma unroll
+        for (int q = 0; q < kMine; ++q)
+            rec[q] = at[(size_t)min(kCoopRows * chunk + c.role + W * q, L.n_batches - 1) * kWave];
+#pragma unroll
+        for (int s = 0; s < kOwn; ++s) {
+            const int k = c.role * kWave + lane_id() + s * W * kWave;
+#pragma unroll
+            for (int h = 0; h < kOctets; ++h) {
+                const int octet = kOctets * chunk + h;
+                tab[s][h] = gmem(c.table)[(size_t)min(octet, (L.n_batches - 1) >> 3) * c.nslot + min(k, c.nslot - 1)];
+                if (k >= c.nslot || 8 * octet >= L.n_batches) tab[s][h] = u32x4{kGatherPad, kGatherPad, kGatherPad, kGatherPad};
+            }
+        }
+    }
+    __device__ __forceinline__ void count() {
+#pragma unroll
+        for (int s = 0; s < kOwn; ++s)
+#pragma unroll
+            for (int h = 0; h < kOctets; ++h) {
+                words[s][h] = 0;
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if (__any(tab[s][h][w] != kGatherPad)) words[s][h] = w + 1;   // a slot's entries lie at the front
+            }
+    }
+};
+
+// The shared part of one evaluation, entered by every wave of the block with
+// its shares of the first chunks. KEEP: the ligand has one chunk, whose share
+// stays in registers; else a share is replaced by that of the chunk after next
+// once used, and those of the first two are back at the end. GRID: the wave
+// that has the grid term (role W - 1), code of its own so that its gathers
+// stay in flight until the pair terms are done.
+template <int SLOTS, int W, bool KEEP, bool GRID>
+__device__ __forceinline__ void coop_pairs(const GridParams& G, SmemC<SLOTS>& sm, const Lig<SLOTS>& L,
+                                           const CoopPairs& c, CoopShare<SLOTS, W> (&share)[KEEP ? 1 : 2]) {
+    using Share = CoopShare<SLOTS, W>;
+    const int lane = lane_id();
+    const int nb = L.n_batches;
+    const int chunks = (nb + kCoopRows - 1) / kCoopRows;
+    const int y_batch = 4 * ((nb - 1) >> 2) + 2;      // the batch whose squares are added x first
+    float x[SLOTS][3], tv[3] = {sm.t[0], sm.t[1], sm.t[2]};
+    GridTaps tap[SLOTS];
+    if constexpr (GRID) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const float4 p = sm.dyn[lane + kWave * s];
+            x[s][0] = p.x; x[s][1] = p.y; x[s][2] = p.z;
+            grid_load<false>(G, L.cls[s], x[s], tv, tap[s]);
+        }
+    }
+    float4 acc[Share::kOwn];
+#pragma unroll
+    for (int s = 0; s < Share::kOwn; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float e_lane = 0.f;
+    auto pairs = [&](int chunk, auto set) {
+        constexpr int b = decltype(set)::value;
+        float4* const pair = c.pair + b * kCoopRows * kPairRow;
+        float* const energy = c.energy + b * kCoopRows * kWave;
+#pragma unroll
+        for (int q = 0; q < Share::kMine; ++q) {
+            const int r = c.role + W * q, batch = kCoopRows * chunk + r;
+            if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);    // two batches in flight
+            if (batch < nb) {
+                const u32x4 rec = share[b].rec[q];
+                const float4 pi = *slot(sm.dyn, rec.x & L.pmask);
+                const float4 pj = *slot(sm.dyn, __builtin_amdgcn_ubfe(rec.x, dockblob::kSlotShift, L.pbits));
+                const PairForce F = pair_force(rec, pi, pj, batch == y_batch);
+                pair[r * kPairRow + lane] = make_float4(F.dx, F.dy, F.dz, F.w);
+                energy[r * kWave + lane] = F.e;
+            }
+        }
+    };
+    auto gather = [&](int chunk, auto set) {
+        constexpr int b = decltype(set)::value;
+        float4* const pair = c.pair + b * kCoopRows * kPairRow;
+        const float* const energy = c.energy + b * kCoopRows * kWave;
+        if constexpr (!KEEP) share[b].count();
+#pragma unroll
+        for (int s = 0; s < Share::kOwn; ++s)
+#pragma unroll
+            for (int h = 0; h < Share::kOctets; ++h) {
+                // four entries at a time, all of an octet's reads ahead of the
+                // sums; an entry is the byte offset of a pair in the octet's
+                // rows, with its sign in bit 15
+                const float4* const rows = pair + h * dockblob::kGatherRows * kPairRow;
+                const u32x4 tab = share[b].tab[s][h];
+                const bool some = share[b].words[s][h] > 0, more = share[b].words[s][h] > 2;
+                float4 f[8];
+                auto read = [&](int k) {
+                    const uint32_t word = tab[k];
+                    f[2 * k] = *slot(const_cast<float4*>(rows), (int)(word & 0x7fffu));
+                    f[2 * k + 1] = *slot(const_cast<float4*>(rows), (int)__builtin_amdgcn_ubfe(word, 16, 15));
+                };
+                auto add = [&](int k) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float4 v = f[2 * k + e];
+                        const uint32_t flip = (e ? tab[k] : tab[k] << 16) & 0x80000000u;
+                        const float w = __uint_as_float(__float_as_uint(v.w) ^ flip);
+                        acc[s].x = fmaf(w, v.x, acc[s].x);
+                        acc[s].y = fmaf(w, v.y, acc[s].y);
+                        acc[s].z = fmaf(w, v.z, acc[s].z);
+                    }
+                };
+                if (some) { read(0); read(1); }
+                if (more) { read(2); read(3); }
+                __builtin_amdgcn_sched_barrier(0);
+                if (some) { add(0); add(1); }
+                if (more) { add(2); add(3); }
+            }
+        if (c.role == W - 2) {
+            float e[kCoopRows];                       // rows no batch filled are read, not used
+#pragma unroll
+            for (int r = 0; r < kCoopRows; ++r) e[r] = energy[r * kWave + lane];
+#pragma unroll
+            for (int r = 0; r < kCoopRows; ++r)
+                if (kCoopRows * chunk + r < nb) e_lane += e[r];
+        }
+        if constexpr (!KEEP) share[b].load(L, c, chunk + 2 < chunks ? chunk + 2 : min(chunk & 1, chunks - 1));
+    };
+    using Set0 = IntC<0>;
+    using Set1 = IntC<KEEP ? 0 : 1>;
+    if (chunks > 0) {
+        pairs(0, Set0());
+        lds_barrier();
+        if constexpr (KEEP) {
+            gather(0, Set0());
+        } else {
+            // one buffer is filled while the other is summed
+            for (int chunk = 0;; chunk += 2) {
+                if (chunk + 1 < chunks) pairs(chunk + 1, Set1());
+                gather(chunk, Set0());
+                if (chunk + 1 >= chunks) break;
+                lds_barrier();
+                if (chunk + 2 < chunks) pairs(chunk + 2, Set0());
+                gather(chunk + 1, Set1());
+                if (chunk + 2 >= chunks) break;
+                lds_barrier();
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < Share::kOwn; ++s) {
+        const int k = c.role * kWave + lane + s * W * kWave;
+        if (k < c.nslot) sm.acc[k] = acc[s];
+    }
+    if (c.role == W - 2) sm.esum[lane] = e_lane;
+    if constexpr (GRID) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            float4 e;
+            grid_term(G, tap[s], L.chg[s][1], L.chg[s][2], x[s], tv, e.x, e.y, e.z, e.w);
+            sm.grid[lane + kWave * s] = e;
+        }
+    }
+    lds_barrier();
+}
+
+// One individual's search by the block (the code of one work unit).
+template <int SLOTS, int W, bool KEEP>
+__device__ __forceinline__ void coop_search(const DevItem& it, int ind, SmemC<SLOTS>& sm, float4* dyn_lds, bool reload,
+                                            const LsParams& p) {
+    constexpr int kBuffers = KEEP ? 1 : 2;
+    const int lane = lane_id();
+    const int wave = uniform((int)threadIdx.x >> 6);
+    // the leaders of the blocks that share a CU sit on different SIMDs
+    const int role = uniform((wave + ((int)blockIdx.x >> 8)) & (W - 1));
+    Lig<SLOTS> L;
+    load_atoms<SLOTS>(it.blob, 0, L);
+    const Header* h = reinterpret_cast<const Header*>(it.blob);
+    CoopPairs c;
+    c.table = uniform_ptr(reinterpret_cast<const u32x4*>(it.blob + h->off_gather));
+    c.pair = dyn_lds;
+    c.energy = reinterpret_cast<float*>(dyn_lds + kBuffers * kCoopRows * kPairRow);
+    c.nslot = L.n_copies * L.stride;
+    c.role = role;
+    if (reload) {
+        fill_tables(it.blob, sm, L.T, L.NF, (int)threadIdx.x, kWave * W);
+        // the zeros that unused gather entries name, one per octet
+        if (threadIdx.x < kBuffers * kCoopRows / dockblob::kGatherRows)
+            c.pair[threadIdx.x * dockblob::kGatherRows * kPairRow + kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    CoopShare<SLOTS, W> share[kBuffers];
+    if (L.n_batches > 0) {
+#pragma unroll
+        for (int k = 0; k < kBuffers; ++k) {
+            share[k].load(L, c, min(k, (L.n_batches - 1) / kCoopRows));
+            share[k].count();
+        }
+    }
+    lds_barrier();
+    if (role != 0) {
+        while (true) {
+            lds_barrier();
+            if (!uniform(sm.go)) return;
+            if (role == W - 1) coop_pairs<SLOTS, W, KEEP, true>(it.grid, sm, L, c, share);
+            else coop_pairs<SLOTS, W, KEEP, false>(it.grid, sm, L, c, share);
+        }
+    }
+    search(it, ind, L.G, it.iterations, p.rho, p.eps, it.final_eval != 0, true, [&](float gene, float& gr) {
+        Rot Rq;
+        float tv[3], x[SLOTS][3], g[SLOTS][3];
+        pose<SLOTS, 1, 4>(sm, L, gene, Rq, tv, x);
+        if (lane < 3) sm.t[lane] = gene;
+        if (lane == 0) sm.go = 1;
+        lds_barrier();
+        coop_pairs<SLOTS, W, KEEP, false>(it.grid, sm, L, c, share);
+        float e_lane = sm.esum[lane];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int a = lane + kWave * s;
+            const float4 e = sm.grid[a];
+            g[s][0] = g[s][1] = g[s][2] = 0.f;
+            const bool ok = a < L.N;
+            if (ok) sum_copies(sm.acc + a, L.n_copies, L.stride, g[s]);
+            g[s][0] += ok ? e.y : 0.f;
+            g[s][1] += ok ? e.z : 0.f;
+            g[s][2] += ok ? e.w : 0.f;
+            e_lane += ok ? e.x : 0.f;
+        }
+        const int var = it.variant;
+        return finish<SLOTS, 1>(sm, L, Rq, x, g, e_lane, [var](float4 v) {
+            switch (var) {
+                case DOCK_REDUCE_MFMA_F32: return sum4<DOCK_REDUCE_MFMA_F32>(v);
+                case DOCK_REDUCE_MFMA_BF16: return sum4<DOCK_REDUCE_MFMA_BF16>(v);
+                case DOCK_REDUCE_MFMA_F16: return sum4<DOCK_REDUCE_MFMA_F16>(v);
+                case DOCK_REDUCE_MFMA_BF16X3: return sum4<DOCK_REDUCE_MFMA_BF16X3>(v);
+                default: return sum4<DOCK_REDUCE_SHUFFLE>(v);
+            }
+        }, gr);
+    });
+    if (lane == 0) sm.go = 0;
+    lds_barrier();
+}
+
+// Persistent kernel of 64 W threads per individual; units and items as in
+// ls_kernel. Every wave of a block takes the same unit and exits once the
+// counter passes the last.
+template <int SLOTS, int W, bool KEEP>
+__global__ __launch_bounds__(64 * W, 2) void ls_kernel_coop(LsParams p) {
+    __shared__ SmemC<SLOTS> sm;
+    extern __shared__ float4 dyn_lds[];
+    int cur_item = -1;
+    while (true) {
+        lds_barrier();                         // the previous unit is done with the LDS
+        if (threadIdx.x == 0) sm.unit = atomicAdd(p.counter, 1);
+        lds_barrier();
+        const int u = uniform(sm.unit);
+        if (u >= p.total_units) break;
+        const int k = item_of_unit(p, u);
+        const DevItem it = load_item(p.items, k);
+        const bool reload = k != cur_item;
+        cur_item = k;
+        coop_search<SLOTS, W, KEEP>(it, u - it.unit_begin, sm, dyn_lds, reload, p);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Two individuals per wave, for ligands of at most 32 atoms and 25 torsions
 // (G = 7 + T <= 32 genes): each 32-lane half of the wave holds one
 // individual, lane j of half h holding atom j and gene j of individual h.
@@ -1459,10 +1852,7 @@ constexpr int kHalf = 32;
 template <bool FORCES>
 struct __align__(16) Smem2T {
     float4 dyn[2][kHalf];               // per half: positions relative to t, sqrt(kElec) q
-    union {
-        float tk[2][kMaxTors + 1][12];  // per half: torsion transforms, identity at kMaxTors
-        float4 acc[2][FORCES ? dockblob::kMaxSlotsTiny : 1];   // per half: pair-force accumulators
-    } u;
+    TorsionAcc<FORCES ? dockblob::kMaxSlotsTiny : 0> u[2];   // per half
     float4 tor[kMaxTors][2];
     uint32_t chain[kMaxFrag][kChain / 4];
 };
@@ -1532,13 +1922,15 @@ __device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2T<FORCES>& s
     L.cls[0] = ii.x;
     L.frag[0] = ok ? ii.y : 0;
     L.orig[0] = ii.z;
+    // the prefix sums' positions are lanes of this half
+    L.torsion = torsion_word(blob, L.T, a - kFirstTorsion) + (uint32_t)(lane & kHalf) * 0x01010000u;
     const Torsion* tr = reinterpret_cast<const Torsion*>(blob + h->off_tors);
     if (fill_lds && lane < L.T) {
         const Torsion t = tr[lane];
-        const int pk = t.a_pos | (t.b_pos << 8) | (t.first << 16) | (t.end << 24);
-        sm.tor[lane][0] = make_float4(t.p[0], t.p[1], t.p[2], __int_as_float(pk));
+        sm.tor[lane][0] = make_float4(t.p[0], t.p[1], t.p[2], 0.f);
         sm.tor[lane][1] = make_float4(t.u[0], t.u[1], t.u[2], 0.f);
     }
+    if (fill_lds && a < 3) sm.u[lane >> 5].write_identity(a);
     const uint32_t* ch = reinterpret_cast<const uint32_t*>(blob + h->off_chain);
     const int n_chain_words = L.NF * (kChain / 4);
     uint32_t* dst = &sm.chain[0][0];
@@ -1564,16 +1956,10 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     const float tx = row_lane<0>(body), ty = row_lane<1>(body), tz = row_lane<2>(body);
     const Rot Rq = rotation(row_lane<3>(body), row_lane<4>(body), row_lane<5>(body), row_lane<6>(body));
 
-    // torsion transforms of this half's individual (T <= 25, so lane 31 of
-    // each half is free to write the identity)
-    const float psi = __shfl(gene, hb + ((7 + j) & (kHalf - 1)));
-    if (j < L.T) {
-        torsion_transform(psi, sm.tor[j][0], sm.tor[j][1], reinterpret_cast<float4*>(sm.u.tk[h][j]));
-    } else if (j == kHalf - 1) {
-        float4* o = reinterpret_cast<float4*>(sm.u.tk[h][kMaxTors]);
-        o[0] = make_float4(1.f, 0.f, 0.f, 0.f);
-        o[1] = make_float4(0.f, 1.f, 0.f, 0.f);
-        o[2] = make_float4(0.f, 0.f, 1.f, 0.f);
+    // torsion transforms of this half's individual
+    const int k = j - kFirstTorsion;
+    if (k >= 0 && k < L.T) {
+        torsion_transform(gene, sm.tor[k][0], sm.tor[k][1], sm.u[h].transforms() + 3 * k);
     }
     wave_sync();
     // atom positions relative to the rotation centre, as in `evaluate`
@@ -1583,7 +1969,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     {
         float y0 = L.y0[0][0], y1 = L.y0[0][1], y2 = L.y0[0][2];
         const uint32_t* row = sm.chain[L.frag[0]];
-        const char* tkh = reinterpret_cast<const char*>(sm.u.tk[h]);
+        const char* tkh = reinterpret_cast<const char*>(sm.u[h].transforms());
         for (int d = 0; d < n_duos; ++d) {
             const uint32_t w = row[d >> 1] >> (16 * (d & 1));
             float4 T[2][3];
@@ -1606,7 +1992,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     float e_lane = 0.f;
     GridTaps tap;
     float4* const dynh = sm.dyn[h];
-    float4* const acch = sm.u.acc[h];
+    float4* const acch = sm.u[h].acc;
     const int pmask = L.pmask;
     auto pos_i = [&](uint32_t w) { return *slot(dynh, w & pmask); };
     auto pos_j = [&](uint32_t w) { return *slot(dynh, __builtin_amdgcn_ubfe(w, dockblob::kSlotShift, L.pbits)); };
@@ -1645,7 +2031,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
             Pi[n] = pos_i(rn.x);
             Pj[n] = pos_j(rn.x);
             __builtin_amdgcn_sched_barrier(0);
-            const PairForce F = pair_force<r == 0 || (decltype(load)::value == 0 && r == 2)>(R[r], Pi[c], Pj[c]);
+            const PairForce F = pair_force(R[r], Pi[c], Pj[c], r == 0 || (decltype(load)::value == 0 && r == 2));
             if constexpr (GRAD) {
                 const float4 ai = *slot(acch, F.si);
                 const float4 aj = *slot(acch, F.sj);
@@ -1675,13 +2061,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     if constexpr (GRAD) {
         wave_sync();
         // each atom adds its copies in copy order
-        if (j < N)
-            for (int c = 0; c < L.n_copies; ++c) {
-                const float4 v = acch[c * L.stride + j];
-                g[0] += v.x;
-                g[1] += v.y;
-                g[2] += v.z;
-            }
+        if (j < N) sum_copies(acch + j, L.n_copies, L.stride, g);
     }
     // grid term
     float e_atom;
@@ -1700,6 +2080,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
         wave_sync();   // the next evaluation rewrites the position table
         return half_sum(e_lane);
     }
+    const float4 bond_a = dynh[L.torsion & 255], bond_b = dynh[(L.torsion >> 8) & 255];
     // block sum of {E, gx, gy, gz} over each half (wavefront shuffle)
     const float4 EG = half_sum4(make_float4(e_lane, g[0], g[1], g[2]));
     // torsion torques: prefix sums of (g, x cross g) within each half; the
@@ -1714,19 +2095,10 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
 #pragma unroll
     for (int c = 0; c < 3; ++c) half_rows(P[3 + c], lo, tq[c]);
     const float4 TQ = make_float4(row_lane<15>(tq[0]), row_lane<15>(tq[1]), row_lane<15>(tq[2]), 0.f);
-    float gpsi = 0.f;
-    {
-        const int pk = j < L.T ? __float_as_int(sm.tor[j][0].w) : (1 << 16) | (1 << 24);
-        const int t_apos = pk & 255, t_bpos = (pk >> 8) & 255;
-        const int hi = ((pk >> 24) & 255) - 1, lo = ((pk >> 16) & 255) - 1;
-        float S[6];
+    float S[6];
 #pragma unroll
-        for (int c = 0; c < 6; ++c)
-            S[c] = __shfl(P[c], hb + (hi & (kHalf - 1))) - __shfl(P[c], hb + (lo & (kHalf - 1)));
-        const float gt = torsion_gradient(S, dynh[t_apos & (kHalf - 1)], dynh[t_bpos & (kHalf - 1)]);
-        gpsi = j < L.T ? gt : 0.f;
-    }
-    grad = gene_gradient(j, EG, TQ, Rq, __shfl(gpsi, hb + ((j - 7) & (kHalf - 1))));
+    for (int c = 0; c < 6; ++c) S[c] = lane_at(P[c], L.torsion >> 24) - lane_at(P[c], L.torsion >> 16);
+    grad = gene_gradient(j, EG, TQ, Rq, torsion_gradient(S, bond_a, bond_b));
     if (atom_out && j < N) {
         float4* o = reinterpret_cast<float4*>(atom_out) + 2 * L.orig[0];
         o[0] = make_float4(x[0], x[1], x[2], e_atom);
@@ -1756,12 +2128,14 @@ __device__ void local_search_two(const DevItem& it, int ind0, int count, Smem2& 
     float bestE = it.best_energy[ind];
     float lastE = it.energy[ind];
     float lastG = 0.f;
-    for (int iter = 0; iter < iterations; ++iter) {
+    const int passes = iterations + (final_eval ? 1 : 0);
+    for (int pass = 0; pass < passes; ++pass) {
         float gr;
         const float E = evaluate2<ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
         lastE = E;
         lastG = gr;
         if (E < bestE) { bestE = E; bx = x; }
+        if (pass == iterations) break;
         gr = act ? gr : 0.f;
         float xn = adadelta(x, gr, rho, eps, ag, ad);
         const bool isq = j >= 3 && j < 7;
@@ -1769,13 +2143,6 @@ __device__ void local_search_two(const DevItem& it, int ind0, int count, Smem2& 
         const float nq2 = (row_lane<3>(q2) + row_lane<4>(q2)) + (row_lane<5>(q2) + row_lane<6>(q2));
         if (isq) xn = (nq2 >= 1e-12f) ? xn * __builtin_amdgcn_rsqf(nq2) : x;
         x = act ? xn : 0.f;
-    }
-    if (final_eval) {
-        float gr;
-        const float E = evaluate2<ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
-        lastE = E;
-        lastG = gr;
-        if (E < bestE) { bestE = E; bx = x; }
     }
     if (!live) return;
     if (act && it.grad && (iterations > 0 || final_eval)) it.grad[o] = lastG;
@@ -1991,6 +2358,22 @@ __global__ __launch_bounds__(1024) void block_sum4_atomic_kernel(const float4* _
     out[idx] = tot;
 }
 
+// Blocks of a kernel that a CU holds at once. The runtime's count divides the
+// LDS by the size asked for, but LDS is given out in granules of 1,280 bytes: 13
+// blocks of 12,416 bytes were launched per CU where 12 fit, and the last one ran
+// as a round of its own (65,536 genotypes of 24 atoms: 80 us instead of 63).
+constexpr size_t kLdsGranule = 1280, kLdsPerCu = 160 * 1024;
+
+bool resident_blocks(int* per_cu, const void* k, int threads, size_t dynamic_lds) {
+    hipFuncAttributes a;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k, threads, dynamic_lds) != hipSuccess ||
+        *per_cu <= 0 || hipFuncGetAttributes(&a, k) != hipSuccess)
+        return false;
+    const size_t granules = (a.sharedSizeBytes + dynamic_lds + kLdsGranule - 1) / kLdsGranule;
+    if (granules) *per_cu = std::min(*per_cu, (int)std::max<size_t>(1, kLdsPerCu / (granules * kLdsGranule)));
+    return true;
+}
+
 template <int SLOTS, int VAR, bool ANY, bool GRAD>
 hipError_t launch_score_k(const GridParams& g, const uint8_t* blob, int n, const float* gen, float* energy,
                           float* grad, float* atom_out, int n_cu, hipStream_t st) {
@@ -2000,10 +2383,7 @@ hipError_t launch_score_k(const GridParams& g, const uint8_t* blob, int n, const
     static std::atomic<int> cached{0};
     int per_cu = cached.load(std::memory_order_relaxed);
     if (per_cu <= 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k), 64, 0) !=
-                hipSuccess ||
-            per_cu <= 0)
-            per_cu = 2;
+        if (!resident_blocks(&per_cu, reinterpret_cast<const void*>(k), 64, 0)) per_cu = 2;
         cached.store(per_cu, std::memory_order_relaxed);
     }
     const long long resident = (long long)per_cu * (n_cu > 0 ? n_cu : 256);
@@ -2112,7 +2492,7 @@ hipError_t launch_score_two(const GridParams& g, const uint8_t* blob, int n, con
     std::atomic<int>& slot = cached[2 * any + forces];
     int per_cu = slot.load(std::memory_order_relaxed);
     if (per_cu <= 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64, 0) != hipSuccess || per_cu <= 0) per_cu = 2;
+        if (!resident_blocks(&per_cu, k, 64, 0)) per_cu = 2;
         slot.store(per_cu, std::memory_order_relaxed);
     }
     const long long pairs = ((long long)n + 1) / 2;
@@ -2164,9 +2544,43 @@ int ls_blocks_per_cu(int mode, int variant_uniform) {
     int nb = cache[m][v].load(std::memory_order_relaxed);
     if (nb > 0) return nb;
     const void* k = ls_kernel_for(mode, variant_uniform);
-    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, ls_block_threads(mode), 0) != hipSuccess) return 0;
+    if (!k || !resident_blocks(&nb, k, ls_block_threads(mode), 0)) return 0;
     cache[m][v].store(nb, std::memory_order_relaxed);
     return nb;
+}
+
+namespace {
+const void* coop_kernel(int mode, int waves, bool keep) {
+    if (mode == kSlots2 && waves == 8)
+        return reinterpret_cast<const void*>(keep ? &ls_kernel_coop<2, 8, true> : &ls_kernel_coop<2, 8, false>);
+    if (mode == kSlots1 && waves == 8)
+        return reinterpret_cast<const void*>(keep ? &ls_kernel_coop<1, 8, true> : &ls_kernel_coop<1, 8, false>);
+    if (mode == kSlots1 && waves == 4)
+        return reinterpret_cast<const void*>(keep ? &ls_kernel_coop<1, 4, true> : &ls_kernel_coop<1, 4, false>);
+    return nullptr;
+}
+size_t coop_lds(bool keep) { return (size_t)kCoopRows * (keep ? 1 : 2) * (kPairRow * sizeof(float4) + kWave * sizeof(float)); }
+}  // namespace
+
+int coop_blocks_per_cu(int mode, int waves, bool keep) {
+    // cached per kernel, as in ls_blocks_per_cu
+    static std::atomic<int> cache[2][2][2];
+    const void* k = coop_kernel(mode, waves, keep);
+    if (!k) return 0;
+    std::atomic<int>& slot = cache[mode == kSlots1][waves == 8][keep];
+    int nb = slot.load(std::memory_order_relaxed);
+    if (nb > 0) return nb;
+    if (!resident_blocks(&nb, k, 64 * waves, coop_lds(keep))) return 0;
+    slot.store(nb, std::memory_order_relaxed);
+    return nb;
+}
+
+hipError_t launch_ls_coop(const LsParams& p, int mode, int waves, bool keep, int grid_blocks, hipStream_t stream) {
+    const void* k = coop_kernel(mode, waves, keep);
+    if (!k) return hipErrorInvalidValue;
+    LsParams pp = p;
+    void* args[] = {&pp};
+    return hipLaunchKernel(k, dim3(grid_blocks), dim3(64 * waves), args, coop_lds(keep), stream);
 }
 
 hipError_t launch_block_sum4(const float* in, float* out, int n_blocks, int threads, int variant,

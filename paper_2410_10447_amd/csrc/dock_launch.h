@@ -88,6 +88,15 @@ hipError_t launch_ls(const LsParams& p, int mode, int variant_uniform, int grid_
 // (mode, variant_uniform); 0 on error.
 int ls_blocks_per_cu(int mode, int variant_uniform);
 
+// One individual per block of `waves` waves, for the one-wave families on
+// corner-expanded maps (mode kSlots1, 4 or 8 waves; kSlots2, 8 waves): any
+// variant, same results bit for bit. `keep`: every ligand of the launch has at
+// most kCoopKeep pair batches, which the waves then hold in registers. Resident
+// blocks per CU (0 on error), and the launch.
+constexpr int kCoopKeep = 16;
+int coop_blocks_per_cu(int mode, int waves, bool keep);
+hipError_t launch_ls_coop(const LsParams& p, int mode, int waves, bool keep, int grid_blocks, hipStream_t stream);
+
 hipError_t launch_block_sum4(const float* in, float* out, int n_blocks, int threads,
                              int variant, int repeat, hipStream_t stream);
 

@@ -650,6 +650,8 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
     h.off_tors = take(sizeof(Torsion) * size_t(T));
     h.off_chain = take(size_t(NF) * kChainStride);
     h.off_plist = take(sizeof(dockblob::PairRec) * size_t(kBatch) * size_t(n_batches));
+    const size_t n_octets = (size_t(n_batches) + 7) / 8, n_slots = size_t(C) * S;
+    h.off_gather = take(sizeof(uint16_t) * n_octets * n_slots * 8);
     h.magic = kMagic;
     h.n_atoms = N;
     h.n_torsions = T;
@@ -703,6 +705,15 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
         tr[k].end = pos[b] + size[b];
     }
     PairRec* pl = reinterpret_cast<PairRec*>(blob.data() + h.off_plist);
+    uint16_t* gather = reinterpret_cast<uint16_t*>(blob.data() + h.off_gather);
+    std::fill(gather, gather + n_octets * n_slots * 8, kGatherNone);
+    // batches come in order, so each slot's entries of a buffer do too
+    static_assert(kGatherRows == 8, "a slot has at most eight entries per buffer");
+    std::vector<uint8_t> n_gather(n_octets * n_slots, 0);
+    auto add_gather = [&](int batch, int lane, uint32_t at, uint32_t copy, uint16_t sign) {
+        const size_t s = size_t(batch / 8) * n_slots + copy * S + at;
+        gather[8 * s + n_gather[s]++] = (uint16_t)(kGatherRow * (batch % 8) + 16 * lane) | sign;
+    };
     auto solv = [&](int i) { return ff.solv[d.cls[i]] + kQSolv * std::fabs((double)d.charge[i]); };
     for (int b = 0; b < n_batches; ++b)
         for (size_t k = 0; k < batch[b].size(); ++k) {
@@ -715,6 +726,8 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
                 o.cm = o.ds = 0.f;
                 continue;
             }
+            add_gather(b, (int)k, r & 127, (r >> 14) & 15, kGatherMinus);
+            add_gather(b, (int)k, (r >> 7) & 127, (r >> 18) & 15, 0);
             const int i = order[r & 127], j = order[(r >> 7) & 127];
             const int ci = d.cls[i], cj = d.cls[j];
             // A / r^12 + B / r^m: 12-10 (5, -6) eps r0^(12, 10) from the
