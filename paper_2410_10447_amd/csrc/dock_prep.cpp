@@ -75,58 +75,145 @@ inline int read_pass(int lane) {
 // write group (mod 8); first-improvement passes until none helps.
 constexpr int kRefinePasses = 12;
 
+// A move's change of the cost is formed without making it: taking x out of a
+// count c and putting y in, and the other way round in d, changes the sums of
+// squares by 2 (c[y] - c[x] + d[x] - d[y]) + 4, x != y. Each count of the pass
+// (group) p is held for the residues of all 32 lanes as one vector of bytes, so
+// that a lane's swaps with all others are tried at once (trying each by making
+// and unmaking it, with the vectors of vectors around it, made the preparation of
+// 300 ligands of 1 to 128 atoms take 1.36 s; now 0.34 s).
+constexpr int kRefineMin = 128;   // cost without any repeat: 4 times 16 lanes read, 8 times 8 written
+constexpr int kRefineMoves = 32 * 33 / 2;
+typedef int8_t Lanes __attribute__((vector_size(32)));
+
+// One byte per lane, read and written singly or as a whole.
+struct LaneBytes {
+    alignas(32) int8_t lane[32] = {};
+    Lanes all() const {
+        Lanes v;
+        std::memcpy(&v, lane, sizeof(v));
+        return v;
+    }
+    void set(const Lanes& v) { std::memcpy(lane, &v, sizeof(v)); }
+};
+
+inline uint32_t swapped_atoms(uint32_t r) {
+    const uint32_t i = r & 127, j = (r >> 7) & 127, ci = (r >> 14) & 15, cj = (r >> 18) & 15;
+    return (r & ~0x3FFFFFu) | j | (i << 7) | (cj << 14) | (ci << 18);
+}
+
 void refine_half(uint32_t* lanes32, int half) {
-    int rc[2][2][16] = {}, wc[4][2][8] = {};
-    auto atom = [&](int l, int role) { return role ? (int)((lanes32[l] >> 7) & 127) : (int)(lanes32[l] & 127); };
-    auto pass = [&](int l) { return read_pass(32 * half + l) & 1; };
-    auto put = [&](int l, int sgn, long long& cost) {
+    // half a change is at most 2 (17 + 17) + 2 (9 + 9): it fits a byte
+    int8_t rc[2][2][16] = {}, wc[4][2][8] = {};     // [pass][role][residue], [group][role][residue]
+    LaneBytes at[2], quad[2];                       // [role]: residues mod 16, mod 8
+    LaneBytes rows[2][2], rows_w[4][2];             // the counts at the lanes' residues
+    LaneBytes in_pass[2], in_group[4];              // -1 in the lanes of the pass, the group
+    int pass[32];
+    for (int l = 0; l < 32; ++l) {
+        pass[l] = read_pass(32 * half + l) & 1;
+        in_pass[pass[l]].lane[l] = in_group[l >> 3].lane[l] = -1;
+    }
+    auto load = [&](int l) {
         for (int role = 0; role < 2; ++role) {
-            const int a = atom(l, role);
-            int& r = rc[pass(l)][role][a & 15];
-            int& w = wc[l >> 3][role][a & 7];
-            if (sgn > 0) { cost += 2 * r + 1; ++r; cost += 2 * w + 1; ++w; }
-            else { --r; cost -= 2 * r + 1; --w; cost -= 2 * w + 1; }
+            at[role].lane[l] = (int8_t)((role ? lanes32[l] >> 7 : lanes32[l]) & 15);
+            quad[role].lane[l] = at[role].lane[l] & 7;
         }
     };
-    auto flip = [&](int l) {
-        const uint32_t r = lanes32[l];
-        const uint32_t i = r & 127, j = (r >> 7) & 127, ci = (r >> 14) & 15, cj = (r >> 18) & 15;
-        lanes32[l] = (r & ~0x3FFFFFu) | j | (i << 7) | (cj << 14) | (ci << 18);
+    auto look_up = [&](int l) {
+        for (int role = 0; role < 2; ++role) {
+            for (int p = 0; p < 2; ++p) rows[p][role].lane[l] = rc[p][role][at[role].lane[l]];
+            for (int g = 0; g < 4; ++g) rows_w[g][role].lane[l] = wc[g][role][quad[role].lane[l]];
+        }
     };
-    long long cost = 0;
-    for (int l = 0; l < 32; ++l) put(l, +1, cost);
-    // first-improvement passes over every lane pair and every lane's atom
-    // swap, until a pass finds nothing better
-    auto try_move = [&](int a, int b) {
-        const long long before = cost;
-        put(a, -1, cost);
-        if (b != a) put(b, -1, cost);
-        if (b == a) flip(a); else std::swap(lanes32[a], lanes32[b]);
-        put(a, +1, cost);
-        if (b != a) put(b, +1, cost);
-        if (cost < before) return true;
-        put(a, -1, cost);
-        if (b != a) put(b, -1, cost);
-        if (b == a) flip(a); else std::swap(lanes32[a], lanes32[b]);
-        put(a, +1, cost);
-        if (b != a) put(b, +1, cost);
-        return false;
+    auto count = [&](int l, int8_t n) {
+        for (int role = 0; role < 2; ++role) {
+            rc[pass[l]][role][at[role].lane[l]] += n;
+            wc[l >> 3][role][quad[role].lane[l]] += n;
+        }
     };
-    for (int pass = 0; pass < kRefinePasses; ++pass) {
-        bool improved = false;
-        for (int a = 0; a < 32; ++a)
-            for (int b = a; b < 32; ++b) improved |= try_move(a, b);
-        if (!improved) break;
+    auto put = [&](int l, int8_t n) {
+        count(l, n);
+        for (int role = 0; role < 2; ++role) {
+            LaneBytes &r = rows[pass[l]][role], &w = rows_w[l >> 3][role];
+            r.set(r.all() + ((at[role].all() == at[role].lane[l]) & n));
+            w.set(w.all() + ((quad[role].all() == quad[role].lane[l]) & n));
+        }
+    };
+    for (int l = 0; l < 32; ++l) {
+        load(l);
+        count(l, 1);
     }
+    for (int l = 0; l < 32; ++l) look_up(l);
+    int cost = 0;
+    for (int role = 0; role < 2; ++role) {
+        for (int r = 0; r < 32; ++r) cost += rc[r >> 4][role][r & 15] * rc[r >> 4][role][r & 15];
+        for (int w = 0; w < 32; ++w) cost += wc[w >> 3][role][w & 7] * wc[w >> 3][role][w & 7];
+    }
+    auto flip_change = [&](int a) {
+        const int x = at[0].lane[a], y = at[1].lane[a], u = x & 7, v = y & 7;
+        const int8_t *r0 = rc[pass[a]][0], *r1 = rc[pass[a]][1], *w0 = wc[a >> 3][0], *w1 = wc[a >> 3][1];
+        return (x == y ? 0 : r0[y] - r0[x] + r1[x] - r1[y] + 2) + (u == v ? 0 : w0[v] - w0[u] + w1[u] - w1[v] + 2);
+    };
+    int8_t change[32];                              // half the change of lane a's swap with lane b
+    auto swap_changes = [&](int a) {
+        const int p = pass[a], g = a >> 3;
+        Lanes sum = {};
+        for (int role = 0; role < 2; ++role) {
+            const int8_t x = at[role].lane[a], u = quad[role].lane[a];
+            const int8_t base = (int8_t)(rc[p ^ 1][role][x] - rc[p][role][x] + 2);
+            sum += (rows[p][role].all() - rows[p ^ 1][role].all() + base) & (at[role].all() != x) & in_pass[p ^ 1].all();
+            Lanes w = rows_w[g][role].all() + (int8_t)(2 - wc[g][role][u]);
+            for (int k = 0; k < 4; ++k) w += (wc[k][role][u] - rows_w[k][role].all()) & in_group[k].all();
+            sum += w & (quad[role].all() != u) & ~in_group[g].all();
+        }
+        std::memcpy(change, &sum, sizeof(change));
+    };
+    // the first lane from `b` on with a negative change, 32 if there is none
+    auto improving = [&](int b) {
+        uint64_t found = 0;                         // a bit per lane, from the bytes' signs
+        for (int k = 0; k < 4; ++k) {
+            uint64_t w;
+            std::memcpy(&w, change + 8 * k, sizeof(w));
+            found |= ((w >> 7 & 0x0101010101010101u) * 0x0102040810204080u >> 56) << (8 * k);
+        }
+        found = found >> b << b;
+        return found ? __builtin_ctzll(found) : 32;
+    };
+    // first-improvement passes over every lane pair and every lane's atom
+    // swap, until every move in turn has found nothing better
+    int idle = 0;
+    for (int round = 0; round < kRefinePasses && cost > kRefineMin; ++round)
+        for (int a = 0; a < 32; ++a) {
+            swap_changes(a);
+            change[a] = (int8_t)flip_change(a);
+            for (int b = a; b < 32; ++b) {
+                const int from = b;
+                b = improving(b);
+                idle += b - from;
+                if (idle >= kRefineMoves) return;
+                if (b == 32) break;
+                idle = 0;
+                cost += 2 * change[b];
+                put(a, -1);
+                if (b != a) put(b, -1);
+                if (b == a) lanes32[a] = swapped_atoms(lanes32[a]); else std::swap(lanes32[a], lanes32[b]);
+                load(a);
+                load(b);
+                put(a, 1);
+                if (b != a) put(b, 1);
+                look_up(a);
+                look_up(b);
+                swap_changes(a);
+            }
+        }
 }
 
 // Splits 16 records whose first-atom and second-atom classes mod 8 each occur
 // exactly twice (a 2-regular bipartite multigraph) into two sets of 8 that
 // each hold every class once per role: alternate edges around each cycle.
-bool two_matchings(const std::vector<uint32_t>& rec, std::vector<int>& side) {
-    const int n = (int)rec.size();
-    if (n != 16) return false;
-    std::vector<int> t(n), h(n);
+bool two_matchings(const uint32_t rec[16], int side[16]) {
+    const int n = 16;
+    int t[n], h[n];
     int ct[8] = {}, ch[8] = {};
     for (int e = 0; e < n; ++e) {
         t[e] = rec[e] & 7;
@@ -135,7 +222,7 @@ bool two_matchings(const std::vector<uint32_t>& rec, std::vector<int>& side) {
         ++ch[h[e]];
     }
     for (int c = 0; c < 8; ++c) if (ct[c] != 2 || ch[c] != 2) return false;
-    side.assign(n, -1);
+    std::fill(side, side + n, -1);
     for (int start = 0; start < n; ++start) {
         if (side[start] >= 0) continue;
         int e = start, s = 0;
@@ -159,32 +246,31 @@ bool two_matchings(const std::vector<uint32_t>& rec, std::vector<int>& side) {
 // chooses cycles of X u Y so that one perfect matching takes 4 records of X
 // and 4 of Y; the rest form the complementary one. m[e] in {0, 1} for the
 // 16 records (X first). False if no subset of cycles has half-length 4.
-bool balanced_pair(const std::vector<uint32_t>& xy, std::vector<int>& m) {
+bool balanced_pair(const uint32_t xy[16], int m[16]) {
     const int n = 16;
-    std::vector<int> cyc(n, -1);
-    std::vector<int> len;
+    int cyc[n], len[n], stack[n], K = 0;
+    std::fill(cyc, cyc + n, -1);
     for (int start = 0; start < n; ++start) {
         if (cyc[start] >= 0) continue;
-        const int id = (int)len.size();
-        len.push_back(0);
-        std::vector<int> stack{start};
+        const int id = K++;
+        int depth = 0;
+        len[id] = 0;
+        stack[depth++] = start;
         cyc[start] = id;
-        while (!stack.empty()) {
-            const int e = stack.back();
-            stack.pop_back();
+        while (depth) {
+            const int e = stack[--depth];
             ++len[id];
             for (int f = 0; f < n; ++f) {
                 if (cyc[f] >= 0) continue;
                 if (((xy[f] & 7) == (xy[e] & 7)) || (((xy[f] >> 7) & 7) == ((xy[e] >> 7) & 7))) {
                     cyc[f] = id;
-                    stack.push_back(f);
+                    stack[depth++] = f;
                 }
             }
         }
     }
-    const int K = (int)len.size();
     // subset of cycles whose X-edge count (half the length) sums to 4
-    std::vector<std::vector<uint8_t>> reach(K + 1, std::vector<uint8_t>(9, 0));
+    uint8_t reach[n + 1][9] = {};
     reach[0][0] = 1;
     for (int k = 0; k < K; ++k)
         for (int s0 = 0; s0 <= 8; ++s0) {
@@ -193,11 +279,10 @@ bool balanced_pair(const std::vector<uint32_t>& xy, std::vector<int>& m) {
             if (s0 + len[k] / 2 <= 8) reach[k + 1][s0 + len[k] / 2] = 1;
         }
     if (!reach[K][4]) return false;
-    std::vector<int> take(K, 0);
+    int take[n] = {};
     int want = 4;
     for (int k = K - 1; k >= 0; --k)
         if (!reach[k][want]) { take[k] = 1; want -= len[k] / 2; }
-    m.assign(n, 0);
     for (int e = 0; e < n; ++e) {
         const bool is_x = e < 8;
         m[e] = (take[cyc[e]] ? (is_x ? 0 : 1) : (is_x ? 1 : 0));
@@ -205,28 +290,32 @@ bool balanced_pair(const std::vector<uint32_t>& xy, std::vector<int>& m) {
     return true;
 }
 
-void place_half(const std::vector<uint32_t>& p0, const std::vector<uint32_t>& p1, int half, uint32_t* out64) {
+void place_half(const uint32_t p0[16], const uint32_t p1[16], int half, uint32_t* out64) {
     uint32_t* lanes32 = out64 + 32 * half;
     // lanes of each (write group, read pass) within the half
-    std::vector<int> slot[4][2];
-    for (int l = 0; l < 32; ++l) slot[l >> 3][read_pass(32 * half + l) & 1].push_back(l);
+    int slot[4][2][4], n_slot[4][2] = {};
+    for (int l = 0; l < 32; ++l) {
+        const int w = l >> 3, p = read_pass(32 * half + l) & 1;
+        slot[w][p][n_slot[w][p]++] = l;
+    }
     // exact: both passes 2-regular on the classes mod 8, and the write groups
     // formed as balanced perfect matchings of X u Y
-    std::vector<int> sa, sb;
+    int sa[16], sb[16];
     if (two_matchings(p0, sa) && two_matchings(p1, sb)) {
-        std::vector<uint32_t> A[2], Bm[2];
-        for (int e = 0; e < 16; ++e) { A[sa[e]].push_back(p0[e]); Bm[sb[e]].push_back(p1[e]); }
+        uint32_t A[2][8], Bm[2][8];
+        int na[2] = {}, nbm[2] = {};
+        for (int e = 0; e < 16; ++e) { A[sa[e]][na[sa[e]]++] = p0[e]; Bm[sb[e]][nbm[sb[e]]++] = p1[e]; }
         for (int pairing = 0; pairing < 2; ++pairing) {
-            std::vector<uint32_t> groups[4][2];
+            uint32_t groups[4][2][4];
             bool ok = true;
             for (int q = 0; q < 2 && ok; ++q) {
-                std::vector<uint32_t> xy(A[q]);
-                const std::vector<uint32_t>& y = Bm[q ^ pairing];
-                xy.insert(xy.end(), y.begin(), y.end());
-                std::vector<int> m;
+                uint32_t xy[16];
+                std::copy(A[q], A[q] + 8, xy);
+                std::copy(Bm[q ^ pairing], Bm[q ^ pairing] + 8, xy + 8);
+                int m[16], n[2][2] = {};
                 ok = balanced_pair(xy, m);
                 if (!ok) break;
-                for (int e = 0; e < 16; ++e) groups[2 * q + m[e]][e < 8 ? 0 : 1].push_back(xy[e]);
+                for (int e = 0; e < 16; ++e) groups[2 * q + m[e]][e < 8 ? 0 : 1][n[m[e]][e < 8 ? 0 : 1]++] = xy[e];
             }
             if (!ok) continue;
             for (int w = 0; w < 4; ++w)
@@ -245,34 +334,41 @@ void place_half(const std::vector<uint32_t>& p0, const std::vector<uint32_t>& p1
 
 // Orients the edges (u[e], v[e]) of a multigraph on 16 vertices along Euler
 // circuits (odd vertices paired by virtual edges): flip[e] = 1 reverses edge e.
-void euler_orient(const std::vector<int>& u, const std::vector<int>& v, std::vector<uint8_t>& flip) {
-    const int n = (int)u.size();
-    std::vector<int> eu(u), ev(v);
-    std::vector<int> deg(16, 0);
-    for (int e = 0; e < n; ++e) { ++deg[eu[e]]; ++deg[ev[e]]; }
+void euler_orient(int n, const int* u, const int* v, uint8_t* flip) {
+    constexpr int kEdges = dockblob::kBatch + 8;   // a batch's pairs, at most one virtual edge per two residues
+    int eu[kEdges], ev[kEdges], deg[16] = {}, m = n;
+    for (int e = 0; e < n; ++e) {
+        eu[e] = u[e];
+        ev[e] = v[e];
+        ++deg[eu[e]];
+        ++deg[ev[e]];
+    }
     int odd = -1;
     for (int r = 0; r < 16; ++r)
         if (deg[r] & 1) {
             if (odd < 0) { odd = r; continue; }
-            eu.push_back(odd); ev.push_back(r); odd = -1;
+            eu[m] = odd;
+            ev[m++] = r;
+            odd = -1;
         }
-    const int m = (int)eu.size();
-    std::vector<std::vector<int>> adj(16);
-    for (int e = 0; e < m; ++e) { adj[eu[e]].push_back(e); if (ev[e] != eu[e]) adj[ev[e]].push_back(e); }
-    std::vector<uint8_t> used(m, 0);
-    std::vector<size_t> next(16, 0);
-    flip.assign(n, 0);
+    uint8_t adj[16][kEdges], used[kEdges] = {};
+    int n_adj[16] = {}, next[16] = {};
+    for (int e = 0; e < m; ++e) {
+        adj[eu[e]][n_adj[eu[e]]++] = (uint8_t)e;
+        if (ev[e] != eu[e]) adj[ev[e]][n_adj[ev[e]]++] = (uint8_t)e;
+    }
+    std::fill(flip, flip + n, 0);
     for (int start = 0; start < 16; ++start) {
         // walk unused edges from `start`, orienting each edge in the walking direction
         int cur = start;
         while (true) {
-            while (next[cur] < adj[cur].size() && used[adj[cur][next[cur]]]) ++next[cur];
-            if (next[cur] == adj[cur].size()) {
+            while (next[cur] < n_adj[cur] && used[adj[cur][next[cur]]]) ++next[cur];
+            if (next[cur] == n_adj[cur]) {
                 // stuck (closed a circuit): continue from any vertex with unused edges
                 int w = -1;
                 for (int r = 0; r < 16 && w < 0; ++r) {
-                    while (next[r] < adj[r].size() && used[adj[r][next[r]]]) ++next[r];
-                    if (next[r] < adj[r].size()) w = r;
+                    while (next[r] < n_adj[r] && used[adj[r][next[r]]]) ++next[r];
+                    if (next[r] < n_adj[r]) w = r;
                 }
                 if (w < 0) break;
                 cur = w;
@@ -289,15 +385,12 @@ void euler_orient(const std::vector<int>& u, const std::vector<int>& v, std::vec
 
 std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uint8_t* use, int N, int S,
                                     int C, std::string& err) {
-    const int B = dockblob::kBatch;
+    constexpr int B = dockblob::kBatch;
     const int n = (int)real.size();
-    std::vector<int> ea(n), eb(n);   // first and second atom of each pair
-    for (int e = 0; e < n; ++e) { ea[e] = real[e] & 127; eb[e] = (real[e] >> 7) & 127; }
-    std::vector<int> ru(n), rv(n);
-    for (int e = 0; e < n; ++e) { ru[e] = ea[e] & 15; rv[e] = eb[e] & 15; }
-    std::vector<uint8_t> flip;
-    euler_orient(ru, rv, flip);
-    std::vector<int> tail(n), head(n);
+    int ru[B], rv[B], tail[B], head[B];   // residues of each pair's first and second atom, as given and as oriented
+    uint8_t flip[B];
+    for (int e = 0; e < n; ++e) { ru[e] = real[e] & 15; rv[e] = (real[e] >> 7) & 15; }
+    euler_orient(n, ru, rv, flip);
     for (int e = 0; e < n; ++e) {
         tail[e] = flip[e] ? rv[e] : ru[e];
         head[e] = flip[e] ? ru[e] : rv[e];
@@ -305,9 +398,9 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
     // Residues used more than 4 times as first (or second) atom cannot be
     // kept apart in 4 groups: set aside as few pairs as needed to bring every
     // residue to <= 4 uses per role, preferring pairs that relieve both ends.
-    std::vector<int> n_first(16, 0), n_second(16, 0);
+    int n_first[16] = {}, n_second[16] = {};
     for (int e = 0; e < n; ++e) { ++n_first[tail[e]]; ++n_second[head[e]]; }
-    std::vector<uint8_t> aside(n, 0);
+    uint8_t aside[B] = {};
     for (int pass = 0; pass < 2; ++pass)
         for (int e = 0; e < n; ++e) {
             if (aside[e]) continue;
@@ -320,8 +413,10 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
         }
     // Kempe-chain colouring of the rest, a bipartite multigraph (first-atom
     // residues, second-atom residues) of maximum degree <= 4, with 4 colours
-    const int K = 4;
-    std::vector<int> at_t(16 * K, -1), at_h(16 * K, -1), col(n, -1);
+    constexpr int K = 4;
+    int at_t[16 * K], at_h[16 * K], col[B];
+    std::fill(at_t, at_t + 16 * K, -1);
+    std::fill(at_h, at_h + 16 * K, -1);
     for (int e = 0; e < n; ++e) {
         if (aside[e]) continue;
         const int t = tail[e], h = head[e];
@@ -330,19 +425,24 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
         for (int c = 0; c < K && b < 0; ++c) if (at_h[h * K + c] < 0) b = c;
         if (at_h[h * K + a] >= 0) {
             // swap colours a and b along the path from h that starts with colour a
-            std::vector<int> path;
+            int path[B], n_path = 0;
             int x = h, want = a;
             bool on_head = true;
             while (true) {
                 const int f = on_head ? at_h[x * K + want] : at_t[x * K + want];
                 if (f < 0) break;
-                path.push_back(f);
+                path[n_path++] = f;
                 x = on_head ? tail[f] : head[f];
                 on_head = !on_head;
                 want = (want == a) ? b : a;
             }
-            for (int f : path) { at_t[tail[f] * K + col[f]] = -1; at_h[head[f] * K + col[f]] = -1; }
-            for (int f : path) {
+            for (int k = 0; k < n_path; ++k) {
+                const int f = path[k];
+                at_t[tail[f] * K + col[f]] = -1;
+                at_h[head[f] * K + col[f]] = -1;
+            }
+            for (int k = 0; k < n_path; ++k) {
+                const int f = path[k];
                 col[f] = (col[f] == a) ? b : a;
                 at_t[tail[f] * K + col[f]] = f;
                 at_h[head[f] * K + col[f]] = f;
@@ -354,11 +454,11 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
     }
     // colour g = lane group g; the pairs set aside go where they add the
     // fewest repeats
-    std::vector<std::vector<int>> groups(4);
+    int groups[4][16], n_group[4] = {};
     LaneCounts lc;
     for (int e = 0; e < n; ++e) {
         if (aside[e]) continue;
-        groups[col[e]].push_back(e);
+        groups[col[e]][n_group[col[e]]++] = e;
         ++lc.c16[0][col[e]][tail[e]];
         ++lc.c16[1][col[e]][head[e]];
     }
@@ -366,49 +466,49 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
         if (!aside[e]) continue;
         int best = -1, best_cost = 0;
         for (int g = 0; g < 4; ++g) {
-            if ((int)groups[g].size() >= 16) continue;
+            if (n_group[g] >= 16) continue;
             const int c = lc.c16[0][g][tail[e]] + lc.c16[1][g][head[e]];
             if (best < 0 || c < best_cost) { best = g; best_cost = c; }
         }
-        groups[best].push_back(e);
+        groups[best][n_group[best]++] = e;
         ++lc.c16[0][best][tail[e]];
         ++lc.c16[1][best][head[e]];
     }
     // free slots (copy, atom): unused copies of real atoms, then every slot of
     // the atoms N .. S-1 past the end
-    std::vector<std::pair<int, int>> free_slots;
-    for (int c = 0; c < C; ++c)
-        for (int a = 0; a < S; ++a)
-            if (a >= N || c >= use[a]) free_slots.push_back({c, a});
-    std::vector<uint8_t> taken(free_slots.size(), 0);
-    auto take_best = [&](int role, int g) -> int {
-        int best = -1, best_cost = 0;
-        for (size_t k = 0; k < free_slots.size(); ++k) {
-            if (taken[k]) continue;
-            const int c = lc.c16[role][g][free_slots[k].second & 15];
-            if (best < 0 || c < best_cost) { best = (int)k; best_cost = c; }
+    // past the end, listed per residue: the next one is the first, in that
+    // order, of a residue that the pass uses least
+    struct Slot { int copy, atom, order; };
+    Slot free_slots[16][dockblob::kMaxSlots / 16];   // S is a multiple of 16, C * S at most kMaxSlots
+    int n_free[16] = {}, next_slot[16] = {};
+    if (n < B)
+        for (int c = 0; c < C; ++c)
+            for (int a = 0; a < S; ++a)
+                if (a >= N || c >= use[a]) free_slots[a & 15][n_free[a & 15]++] = {c, a, c * S + a};
+    auto take_best = [&](int role, int g) -> const Slot* {
+        int best = -1;
+        for (int r = 0; r < 16; ++r) {
+            if (next_slot[r] == n_free[r]) continue;
+            const int c = lc.c16[role][g][r], least = best < 0 ? 0 : lc.c16[role][g][best];
+            if (best < 0 || c < least ||
+                (c == least && free_slots[r][next_slot[r]].order < free_slots[best][next_slot[best]].order))
+                best = r;
         }
-        if (best >= 0) {
-            taken[best] = 1;
-            ++lc.c16[role][g][free_slots[best].second & 15];
-        }
-        return best;
+        if (best < 0) return nullptr;
+        ++lc.c16[role][g][best];
+        return &free_slots[best][next_slot[best]++];
     };
     // colour g becomes read pass g: half g / 2, parity g % 2
-    std::vector<std::vector<uint32_t>> pass_rec(4);
+    uint32_t pass_rec[4][16];
     for (int g = 0; g < 4; ++g) {
-        std::vector<uint32_t>& rec = pass_rec[g];
-        for (int e : groups[g]) {
-            const uint32_t r = real[e];
-            if (!flip[e]) { rec.push_back(r); continue; }
-            const uint32_t i = r & 127, j = (r >> 7) & 127, ci = (r >> 14) & 15, cj = (r >> 18) & 15;
-            rec.push_back((r & ~0x3FFFFFu) | j | (i << 7) | (cj << 14) | (ci << 18));
+        for (int l = 0; l < n_group[g]; ++l) {
+            const int e = groups[g][l];
+            pass_rec[g][l] = flip[e] ? swapped_atoms(real[e]) : real[e];
         }
-        for (int l = (int)groups[g].size(); l < 16; ++l) {
-            const int u = take_best(0, g), v = take_best(1, g);
-            if (u < 0 || v < 0) { err = "internal: no free accumulator slots for batch padding"; return {}; }
-            rec.push_back(dockblob::make_pad_record(free_slots[u].second, free_slots[v].second,
-                                                    free_slots[u].first, free_slots[v].first));
+        for (int l = n_group[g]; l < 16; ++l) {
+            const Slot *u = take_best(0, g), *v = take_best(1, g);
+            if (!u || !v) { err = "internal: no free accumulator slots for batch padding"; return {}; }
+            pass_rec[g][l] = dockblob::make_pad_record(u->atom, v->atom, u->copy, v->copy);
         }
     }
     std::vector<uint32_t> out(B);
@@ -487,21 +587,20 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
     std::vector<int> pos(N), size(N, 1);
     for (int p = 0; p < N; ++p) pos[order[p]] = p;
     for (int p = N - 1; p > 0; --p) size[parent[order[p]]] += size[order[p]];
-    // bond-graph distances (breadth-first from every atom; rings make them
-    // shorter than depth-first tree paths)
-    std::vector<int> gdist(size_t(N) * N, -1);
+    // atoms fewer than four bonds apart (breadth-first to depth 3 from every
+    // atom; rings make distances shorter than depth-first tree paths)
+    std::vector<uint8_t> near(size_t(N) * N, 0);
     {
         std::vector<int> queue(N);
         for (int s0 = 0; s0 < N; ++s0) {
-            int* dist = &gdist[size_t(s0) * N];
+            uint8_t* seen = &near[size_t(s0) * N];
             int head = 0, tail = 0;
-            dist[s0] = 0;
+            seen[s0] = 1;
             queue[tail++] = s0;
-            while (head < tail) {
-                const int u = queue[head++];
-                for (int v : adj[u])
-                    if (dist[v] < 0) { dist[v] = dist[u] + 1; queue[tail++] = v; }
-            }
+            for (int level = 0; level < 3; ++level)
+                for (const int end = tail; head < end; ++head)
+                    for (int v : adj[queue[head]])
+                        if (!seen[v]) { seen[v] = 1; queue[tail++] = v; }
         }
     }
 
@@ -544,20 +643,23 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
         chain[k + 1].push_back(k);
         max_depth = std::max(max_depth, (int)chain[k + 1].size());
     }
-    auto graph_dist = [&](int i, int j) { return gdist[size_t(i) * N + j]; };
+    std::vector<int> donor(N), acceptor(N);
+    for (int i = 0; i < N; ++i) {
+        donor[i] = role_index(ff.donor, d.cls[i]);
+        acceptor[i] = role_index(ff.acceptor, d.cls[i]);
+    }
     // kept pairs in depth-first positions (p < q), with their 12-10 table index
     struct KeptPair { int p, q, hb, table; };
     std::vector<KeptPair> plist;
     for (int p = 0; p < N; ++p)
         for (int q = p + 1; q < N; ++q) {
             const int i = order[p], j = order[q];
-            if (frag[i] == frag[j] || graph_dist(i, j) < 4) continue;
-            const int ci = d.cls[i], cj = d.cls[j];
+            if (frag[i] == frag[j] || near[size_t(i) * N + j]) continue;
             int table = 0, hb = 0;
-            if (role_index(ff.donor, ci) >= 0 && role_index(ff.acceptor, cj) >= 0) {
-                hb = 1; table = 2 * role_index(ff.donor, ci) + role_index(ff.acceptor, cj);
-            } else if (role_index(ff.acceptor, ci) >= 0 && role_index(ff.donor, cj) >= 0) {
-                hb = 1; table = 2 * role_index(ff.donor, cj) + role_index(ff.acceptor, ci);
+            if (donor[i] >= 0 && acceptor[j] >= 0) {
+                hb = 1; table = 2 * donor[i] + acceptor[j];
+            } else if (acceptor[i] >= 0 && donor[j] >= 0) {
+                hb = 1; table = 2 * donor[j] + acceptor[i];
             }
             plist.push_back({p, q, hb, table});
         }
@@ -583,41 +685,56 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
     }
     std::vector<int> degp(N, 0);
     for (const KeptPair& pr : plist) { ++degp[pr.p]; ++degp[pr.q]; }
-    std::vector<int> porder(plist.size());
-    for (size_t k = 0; k < porder.size(); ++k) porder[k] = (int)k;
-    std::stable_sort(porder.begin(), porder.end(), [&](int a, int b) {
-        return std::max(degp[plist[a].p], degp[plist[a].q]) > std::max(degp[plist[b].p], degp[plist[b].q]);
-    });
     int maxdeg = 0;
     for (int v = 0; v < N; ++v) maxdeg = std::max(maxdeg, degp[v]);
+    // the pairs by decreasing degree, equal ones in order (a counting sort)
+    std::vector<int> porder(plist.size()), first(maxdeg + 2, 0);
+    auto degree = [&](const KeptPair& pr) { return std::max(degp[pr.p], degp[pr.q]); };
+    for (const KeptPair& pr : plist) ++first[maxdeg - degree(pr) + 1];
+    for (int g = 0; g <= maxdeg; ++g) first[g + 1] += first[g];
+    for (size_t k = 0; k < plist.size(); ++k) porder[first[maxdeg - degree(plist[k])]++] = (int)k;
     int nb = std::max((n_pairs + kBatch - 1) / kBatch, (maxdeg + C - 1) / C);
     std::vector<std::vector<uint32_t>> batch;      // records
+    // The score of a pair in every batch is the sum of five rows of costs (the
+    // two atoms' uses, their residues' excess, the fill), each one vector of the
+    // batches, updated where a pair is placed: the compiler adds and compares
+    // four batches at a time.
+    constexpr int kNone = 1 << 28;                 // more than any score: an atom or a batch that is full
+    constexpr int kOver = 1000000, kUse = 1000;    // excess costs more than any uses, uses more than any fill
     while (true) {
         batch.assign(nb, {});
-        std::vector<int> cnt(nb, 0);
         std::vector<uint8_t> use(size_t(nb) * N, 0);
-        std::vector<int> rload(size_t(nb) * 16, 0);   // pair ends per residue mod 16
+        std::vector<int> load(size_t(nb) * 16, 0);              // pair ends per residue mod 16
+        std::vector<int> use_cost(size_t(N) * nb, 0);           // [atom][batch]
+        std::vector<int> over_cost(size_t(2) * 16 * nb, 0);     // [ends added - 1][residue][batch]
+        std::vector<int> fill(nb, 0), score(nb);
+        auto add_end = [&](int b, int atom) {
+            const int n = ++use[size_t(b) * N + atom], r = atom & 15, l = ++load[size_t(b) * 16 + r];
+            use_cost[size_t(atom) * nb + b] = n >= C ? kNone : n * kUse;
+            for (int ends = 1; ends <= 2; ++ends)
+                over_cost[size_t(16 * (ends - 1) + r) * nb + b] = kOver * std::max(0, l + ends - 8);
+            return n - 1;
+        };
         bool placed_all = true;
         for (int k : porder) {
             const KeptPair& pr = plist[k];
             const int rp = pr.p & 15, rq = pr.q & 15;
-            int best = -1;
-            long long best_score = 0;
-            for (int b = 0; b < nb; ++b) {
-                const int up = use[size_t(b) * N + pr.p], uq = use[size_t(b) * N + pr.q];
-                if (cnt[b] >= kBatch || up >= C || uq >= C) continue;
-                const int* rl = &rload[size_t(b) * 16];
-                const int over = rp == rq ? std::max(0, rl[rp] + 2 - 8)
-                                          : std::max(0, rl[rp] + 1 - 8) + std::max(0, rl[rq] + 1 - 8);
-                const long long score = -(long long)over * 1000000 - (up + uq) * 1000 - cnt[b];
-                if (best < 0 || score > best_score) { best = b; best_score = score; }
-            }
-            if (best < 0) { placed_all = false; break; }
-            const int ci = use[size_t(best) * N + pr.p]++;
-            const int cj = use[size_t(best) * N + pr.q]++;
-            ++rload[size_t(best) * 16 + rp];
-            ++rload[size_t(best) * 16 + rq];
-            ++cnt[best];
+            const int *up = &use_cost[size_t(pr.p) * nb], *uq = &use_cost[size_t(pr.q) * nb];
+            const int *op = &over_cost[size_t(rp == rq ? 16 + rp : rp) * nb], *oq = &over_cost[size_t(rq) * nb];
+            const int both = rp != rq;             // else the first row counts both ends
+            int* sc = score.data();
+            const int* fl = fill.data();
+            int least = kNone;
+            if (both)
+                for (int b = 0; b < nb; ++b) sc[b] = up[b] + uq[b] + fl[b] + op[b] + oq[b];
+            else
+                for (int b = 0; b < nb; ++b) sc[b] = up[b] + uq[b] + fl[b] + op[b];
+            for (int b = 0; b < nb; ++b) least = std::min(least, sc[b]);
+            if (least >= kNone) { placed_all = false; break; }
+            int best = 0;
+            while (sc[best] != least) ++best;
+            const int ci = add_end(best, pr.p), cj = add_end(best, pr.q);
+            if (++fill[best] == kBatch) fill[best] = kNone;
             batch[best].push_back(dockblob::make_record(pr.p, pr.q, ci, cj, pr.hb, pr.table));
         }
         if (placed_all) {
@@ -714,6 +831,9 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
         const size_t s = size_t(batch / 8) * n_slots + copy * S + at;
         gather[8 * s + n_gather[s]++] = (uint16_t)(kGatherRow * (batch % 8) + 16 * lane) | sign;
     };
+    // 12-6 coefficients of two classes, formed where a pair first needs them
+    struct VdW { bool known; float c12, cm; };
+    std::vector<VdW> vdw(size_t(ff.n_classes) * ff.n_classes, VdW{false, 0.f, 0.f});
     auto solv = [&](int i) { return ff.solv[d.cls[i]] + kQSolv * std::fabs((double)d.charge[i]); };
     for (int b = 0; b < n_batches; ++b)
         for (size_t k = 0; k < batch[b].size(); ++k) {
@@ -738,10 +858,14 @@ int32_t prepare(const dock_ligand_desc& d, Prepared& P, std::string& err) {
                 o.c12 = (float)(5.0 * eps * std::pow(r0, 12));
                 o.cm = (float)(-6.0 * eps * std::pow(r0, 10));
             } else {
-                const double r0 = ff.radius[ci] + ff.radius[cj];
-                const double eps = std::sqrt(ff.eps[ci] * ff.eps[cj]);
-                o.c12 = (float)(eps * std::pow(r0, 12));
-                o.cm = (float)(-2.0 * eps * std::pow(r0, 6));
+                VdW& w = vdw[size_t(ci) * ff.n_classes + cj];
+                if (!w.known) {
+                    const double r0 = ff.radius[ci] + ff.radius[cj];
+                    const double eps = std::sqrt(ff.eps[ci] * ff.eps[cj]);
+                    w = {true, (float)(eps * std::pow(r0, 12)), (float)(-2.0 * eps * std::pow(r0, 6))};
+                }
+                o.c12 = w.c12;
+                o.cm = w.cm;
             }
             o.ds = (float)(solv(i) * ff.vol[cj] + solv(j) * ff.vol[ci]);
         }
