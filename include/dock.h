@@ -506,6 +506,18 @@ int32_t dock_gather_rows(const float* src_dev, int32_t n_src, int32_t row_floats
 int32_t dock_scatter_rows(const float* src_dev, int32_t m, int32_t row_floats, const int32_t* index_dev,
                           int32_t n_dst, float* dst_dev, void* stream);
 
+/* -------------------------------------------------------------------------
+ * dock_ls_start: the state of a local search before its first step, one launch:
+ * genotype and best_genotype are copies of genotypes_dev [n][n_genes], acc_g2 and
+ * acc_dx2 zeros, best_energy [n] +infinity, energy [n] NaN, iters_done [n] int32
+ * zeros. Arrays are float32 (but iters_done), device, and distinct. n == 0 is a
+ * no-op. Errors: DOCK_EINVAL on n < 0, n_genes < 1, more than 2^31 - 1 genes,
+ * NULL or misaligned arrays.
+ * ---------------------------------------------------------------------- */
+int32_t dock_ls_start(const float* genotypes_dev, int32_t n, int32_t n_genes, float* genotype, float* acc_g2,
+                      float* acc_dx2, float* best_genotype, float* best_energy, float* energy,
+                      int32_t* iters_done, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -810,6 +810,24 @@ int32_t dock_ga_step(const dock_ga_step_desc* d, void* stream) {
     return ok();
 }
 
+int32_t dock_ls_start(const float* genotypes, int32_t n, int32_t n_genes, float* genotype, float* acc_g2,
+                      float* acc_dx2, float* best_genotype, float* best_energy, float* energy, int32_t* iters_done,
+                      void* stream) {
+    if (n < 0 || n_genes < 1) return fail(DOCK_EINVAL, "dock_ls_start: bad sizes");
+    if ((int64_t)n * n_genes > 2147483647LL) return fail(DOCK_EINVAL, "dock_ls_start: more than 2^31 - 1 genes");
+    if (n == 0) return ok();
+    const void* arrays[] = {genotypes, genotype, acc_g2, acc_dx2, best_genotype, best_energy, energy, iters_done};
+    for (const void* a : arrays) {
+        if (!a) return fail(DOCK_EINVAL, "dock_ls_start: NULL pointer");
+        if (!aligned(a, 4)) return fail(DOCK_EINVAL, "dock_ls_start: arrays must be 4-byte aligned");
+    }
+    const docklaunch::LsStartParams p{genotypes, genotype, acc_g2, acc_dx2, best_genotype, best_energy, energy,
+                                      iters_done, n, n_genes};
+    hipError_t e = docklaunch::launch_ls_start(p, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_fail(e, "dock_ls_start launch");
+    return ok();
+}
+
 int32_t dock_select_rows(const float* draws, int32_t n, float rate, int32_t* index, int32_t* count,
                          void* stream) {
     if (n < 0) return fail(DOCK_EINVAL, "dock_select_rows: n < 0");

@@ -27,6 +27,7 @@ hipError_t launch_expand_corners(const GridParams&, float*, hipStream_t) { retur
 hipError_t launch_sw(const GridParams&, const uint8_t*, int, int, const SwParams&, hipStream_t) {
     return hipErrorNoDevice;
 }
+hipError_t launch_ls_start(const LsStartParams&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_ga_step(const GaParams&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_select_rows(const float*, int, float, int32_t*, int32_t*, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_move_rows(bool, const float*, float*, const int32_t*, int, int, int, hipStream_t) {

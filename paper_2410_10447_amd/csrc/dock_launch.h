@@ -121,6 +121,16 @@ hipError_t launch_sw(const GridParams& g, const uint8_t* blob, int slots, int va
                      hipStream_t stream);
 
 // One GA generation step (the operators of dock_ga_step).
+// The state of a search before its first step (dock_ls_start).
+struct LsStartParams {
+    const float* source;      // [n][n_genes]
+    float *genotype, *acc_g2, *acc_dx2, *best_genotype;   // [n][n_genes]
+    float *best_energy, *energy;                          // [n]
+    int32_t* iters_done;                                  // [n]
+    int32_t n, n_genes;
+};
+hipError_t launch_ls_start(const LsStartParams& p, hipStream_t stream);
+
 struct GaParams {
     const float* genotypes;   // [n_runs][pop][n_genes]
     const float* energies;    // [n_runs][pop]

@@ -52,7 +52,7 @@ ABI_SYMBOLS = (
     "dock_grids_corner_bytes", "dock_grids_bind_corners",
     "dock_create_ligand", "dock_ligand_info_get", "dock_ligand_export", "dock_ligand_upload",
     "dock_destroy_ligand", "dock_score_batch", "dock_ls_workspace_bytes",
-    "dock_select_rows", "dock_gather_rows", "dock_scatter_rows",
+    "dock_select_rows", "dock_gather_rows", "dock_scatter_rows", "dock_ls_start",
     "dock_local_search_batch", "dock_local_search_batch_static", "dock_ls_launches", "dock_block_sum4",
     "dock_ga_step", "dock_solis_wets_batch",
 )
@@ -159,6 +159,7 @@ def lib():
         "dock_select_rows": ([vp, i32, C.c_float, vp, vp, vp], i32),
         "dock_gather_rows": ([vp, i32, i32, vp, i32, vp, vp], i32),
         "dock_scatter_rows": ([vp, i32, i32, vp, i32, vp, vp], i32),
+        "dock_ls_start": ([vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp], i32),
         "dock_solis_wets_batch": ([vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, C.POINTER(SwOpts), vp, vp], i32),
     }
     for name, (args, res) in sig.items():
@@ -215,6 +216,21 @@ def _need(name, t, shape, dtype, device=None, placement=True):
         raise ValueError(f"{name}: must be a CUDA tensor")
     if device is not None and t.device != device:
         raise ValueError(f"{name}: on {t.device}, expected {device}")
+
+
+def _plain_rows(t) -> bool:
+    """Whether `t` is a float32 [n, G] matrix that a kernel on the current device
+    may read by its address: an ordinary CUDA tensor outside of autograd, of
+    function transforms and of modes that follow tensor operations."""
+    import torch
+    return (type(t) is torch.Tensor and t.is_cuda and t.dtype == torch.float32 and t.layout == torch.strided
+            and t.dim() == 2 and t.shape[1] > 0 and t.numel() < 2 ** 31 and not t.requires_grad
+            and not t.is_conj() and not t.is_neg()
+            and t.device.index == torch.cuda.current_device()
+            and torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
+            and torch._C._functorch.peek_interpreter_stack() is None
+            and torch.autograd.forward_ad._current_level < 0
+            and torch._C._get_tracing_state() is None and not torch.compiler.is_compiling())
 
 
 # ---------------------------------------------------------------------------
@@ -407,6 +423,15 @@ class LSState:
     @classmethod
     def start(cls, genotypes):
         import torch
+        if _plain_rows(genotypes):
+            src = genotypes.contiguous()
+            n, G = src.shape
+            g, g2, dx2, best = (torch.empty_like(src) for _ in range(4))
+            best_e, e = (torch.empty(n, dtype=torch.float32, device=src.device) for _ in range(2))
+            done = torch.empty(n, dtype=torch.int32, device=src.device)
+            _check(lib().dock_ls_start(src.data_ptr(), n, G, *(t.data_ptr() for t in (g, g2, dx2, best, best_e, e, done)),
+                                       _stream_handle()))
+            return cls(g, g2, dx2, best, best_e, e, done)
         g = genotypes.contiguous().clone()
         n = g.shape[0]
         return cls(g, torch.zeros_like(g), torch.zeros_like(g), g.clone(),
