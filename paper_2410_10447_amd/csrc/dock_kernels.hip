@@ -364,6 +364,7 @@ struct Lig {
     int cls[SLOTS];
     int frag[SLOTS];
     int orig[SLOTS];                // original atom index
+    uint32_t chain[SLOTS];          // the fragment's first four enclosing torsions
     // the torsion of this lane's gene (gene 7 + k is torsion k's angle): depth-first
     // positions of the bond atoms a, b, and of the atoms before the first and
     // at the end of the moving range, a | b << 8 | (first - 1) << 16 | (end - 1) << 24
@@ -376,6 +377,12 @@ __device__ __forceinline__ uint32_t torsion_word(const uint8_t* blob, int T, int
     if (k < 0 || k >= T) return 0;
     const Torsion& t = reinterpret_cast<const Torsion*>(blob + reinterpret_cast<const Header*>(blob)->off_tors)[k];
     return (uint32_t)t.a_pos | (uint32_t)t.b_pos << 8 | (uint32_t)(t.first - 1) << 16 | (uint32_t)(t.end - 1) << 24;
+}
+
+// First word of a fragment's chain (the rest is read from LDS where it is needed).
+__device__ __forceinline__ uint32_t chain_word(const uint8_t* blob, int frag) {
+    const int off = reinterpret_cast<const Header*>(blob)->off_chain;
+    return reinterpret_cast<const uint32_t*>(blob + off)[frag * (kChain / 4)];
 }
 
 // Header fields and this wave's atoms (`wv`: which 64 x SLOTS of them).
@@ -413,6 +420,7 @@ __device__ __forceinline__ void load_atoms(const uint8_t* __restrict__ blob, int
         L.cls[s] = ii.x;
         L.frag[s] = ok ? ii.y : 0;
         L.orig[s] = ii.z;
+        L.chain[s] = chain_word(blob, L.frag[s]);
     }
     L.torsion = torsion_word(blob, L.T, lane - kFirstTorsion);
 }
@@ -704,6 +712,24 @@ __device__ __forceinline__ PairForce pair_force(u32x4 pr, float4 pi, float4 pj, 
     return o;
 }
 
+// The pair records of a wave's batches, LANES to a row, through a buffer resource:
+// a load past the last row gives zeros, whose positions may be read, so prefetches
+// need no clamp. Rows are loaded in groups of four from a scalar row offset, which
+// must not exceed the end (the resource's bound is checked against the rest).
+template <int LANES>
+struct PairRecords {
+    static constexpr int kRow = LANES * (int)sizeof(u32x4);
+    __amdgpu_buffer_rsrc_t rsrc;
+    int lane_off;
+    __device__ __forceinline__ PairRecords(const u32x4* first, int rows, int lane)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(first), 0, rows * kRow, kBufferWord3)),
+          lane_off(lane * (int)sizeof(u32x4)) {}
+    // row `q` (0 to 3) of the group that starts at byte `group`
+    __device__ __forceinline__ u32x4 load(int group, int q) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off + q * kRow, group, 0);
+    }
+};
+
 // Accumulator slot at a byte offset (a multiple of 16) from `base`.
 __device__ __forceinline__ float4* slot(float4* base, int byte_offset) {
     return reinterpret_cast<float4*>(
@@ -817,6 +843,32 @@ __device__ __forceinline__ float adadelta(float x, float gr, float rho, float ep
     return fmaf(rate, gr, x);
 }
 
+// Applies the torsions that enclose an atom, innermost first: `first` holds the
+// four innermost, `row` all, four to a word; the transforms are read LEVELS at a
+// time. Levels past the atom's depth apply the identity, so every lane takes the
+// same (uniform) number of LDS round trips. Up to four levels need no read of the
+// row, which a lone wave would wait for.
+template <int LEVELS>
+__device__ __forceinline__ void apply_chain(uint32_t first, const uint32_t* row, const float4* transforms, int max_depth,
+                                            float& y0, float& y1, float& y2) {
+    static_assert(LEVELS == 2 || LEVELS == 4, "a chain word holds four levels");
+    uint32_t w = first;
+    for (int d = 0; d < max_depth; d += LEVELS) {
+        if (d >= 4 && d % 4 == 0) w = row[d >> 2];
+        float4 T[LEVELS][3];
+#pragma unroll
+        for (int q = 0; q < LEVELS; ++q) {
+            const unsigned k = (w >> (8 * q)) & 255u;
+            const float4* t = reinterpret_cast<const float4*>(__builtin_assume_aligned(
+                reinterpret_cast<const char*>(transforms) + __umul24(k, 48u), 16));
+            T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
+        }
+#pragma unroll
+        for (int q = 0; q < LEVELS; ++q) apply_transform(T[q], y0, y1, y2);
+        if constexpr (LEVELS == 2) w >>= 16;
+    }
+}
+
 // Atom positions of the individual whose genes this wave holds: relative to
 // the translation genes `tv`, in registers (x) and in the LDS position table.
 template <int SLOTS, int WAVES, int LEVELS = 2, class SM>
@@ -844,29 +896,11 @@ __device__ __forceinline__ void pose(SM& sm, const Lig<SLOTS>& L, float gene, Ro
     // separations, torques and torsion axes are translation invariant and
     // keep the precision of the small local coordinates.
     tv[0] = tx; tv[1] = ty; tv[2] = tz;
-    static_assert(LEVELS == 2 || LEVELS == 4, "a chain word holds four levels");
-    const int n_trips = (L.max_depth + LEVELS - 1) / LEVELS;   // LDS round trips, LEVELS levels each
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         const int a = lane + kWave * (s + L.wv);
         float y0 = L.y0[s][0], y1 = L.y0[s][1], y2 = L.y0[s][2];
-        // one word of torsion indices per four levels; levels past the atom's
-        // depth apply the identity, so every lane takes the same (uniform)
-        // number of trips
-        const uint32_t* row = sm.chain[L.frag[s]];
-        for (int d = 0; d < n_trips; ++d) {
-            const uint32_t w = LEVELS == 4 ? row[d] : row[d >> 1] >> (16 * (d & 1));
-            float4 T[LEVELS][3];
-#pragma unroll
-            for (int q = 0; q < LEVELS; ++q) {
-                const unsigned k = (w >> (8 * q)) & 255u;
-                const float4* t = reinterpret_cast<const float4*>(__builtin_assume_aligned(
-                    reinterpret_cast<const char*>(sm.u.transforms()) + __umul24(k, 48u), 16));
-                T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
-            }
-#pragma unroll
-            for (int q = 0; q < LEVELS; ++q) apply_transform(T[q], y0, y1, y2);
-        }
+        apply_chain<LEVELS>(L.chain[s], sm.chain[L.frag[s]], sm.u.transforms(), L.max_depth, y0, y1, y2);
         rotate(Rq, y0, y1, y2, x[s]);
         sm.dyn[a] = make_float4(x[s][0], x[s][1], x[s][2], kSqrtElec * L.chg[s][1]);
     }
@@ -982,6 +1016,21 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                           float& grad, float* atom_out) {
     const int lane = lane_id();
     const int N = L.N;
+    // this wave's batches, the first four of which are loaded ahead of the pose (a
+    // lone wave waited 500 of 11,600 cycles for them: with that, the chain words in
+    // registers and no clamps 3000 individuals of 48 atoms take 2,323 us for 301
+    // evaluations instead of 2,385, 50,001 energies 84.8 instead of 89.0; with several waves per
+    // individual, wave w takes the w-th of WAVES consecutive runs of
+    // ceil(n_batches / WAVES) batches, the last of which may be short or empty)
+    const int run = (L.n_batches + WAVES - 1) / WAVES;
+    const int b0 = WAVES == 1 ? 0 : min(L.wv * run, L.n_batches);
+    const int nb = WAVES == 1 ? L.n_batches : min(L.n_batches - b0, run);
+    using Records = PairRecords<kWave>;
+    const Records records(L.plist + b0 * kWave, nb, lane);
+    u32x4 R[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) R[q] = records.load(0, q);
+
     Rot Rq;
     float tv[3], x[SLOTS][3];
     pose<SLOTS, WAVES>(sm, L, gene, Rq, tv, x);
@@ -1003,27 +1052,17 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         // positions of batch k + 1 from LDS before computing batch k, and
         // loads the record of batch k + 4 (records live four steps, positions
         // two; register sets indexed by k mod 4 and mod 2, steps unrolled by
-        // four). Prefetch indices are clamped to the last batch.
+        // four).
         static_assert(WAVES == 1, "the energy-only evaluation is one wave per individual");
-        const int nb = L.n_batches;
         const int pmask = L.pmask;
         auto pos_i = [&](uint32_t w) { return *slot(sm.dyn, w & pmask); };
         auto pos_j = [&](uint32_t w) { return *slot(sm.dyn, __builtin_amdgcn_ubfe(w, dockblob::kSlotShift, L.pbits)); };
         if (nb > 0) {
-            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<u32x4*>(L.plist), 0, nb * kWave * (int)sizeof(u32x4), kBufferWord3);
-            const int lane_off = lane * (int)sizeof(u32x4);
-            auto record = [&](int b) -> u32x4 {
-                return __builtin_amdgcn_raw_buffer_load_b128(
-                    prsrc, lane_off, uniform(min(b, nb - 1)) * kWave * (int)sizeof(u32x4), 0);
-            };
-            u32x4 R[4];
             float4 Pi[2], Pj[2];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) R[q] = record(q);
             Pi[0] = pos_i(R[0].x);
             Pj[0] = pos_j(R[0].x);
             int k = 0;
+            int group = 4 * Records::kRow;    // the rows of batches k + 4 to k + 7, k mod 4 = 0
             auto step = [&](auto residue, auto load) {
                 constexpr int r = decltype(residue)::value;  // k mod 4
                 constexpr int c = r & 1, n = (r + 1) & 1;
@@ -1034,7 +1073,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
                 constexpr bool last = decltype(load)::value == 0;
                 constexpr bool xfirst = (TRIAL && r == 0) || (last && r == 2);
                 e_lane += pair_force(R[r], Pi[c], Pj[c], xfirst).e;
-                if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
+                if constexpr (decltype(load)::value != 0) R[r] = records.load(group, r);
                 __builtin_amdgcn_sched_barrier(0);
                 ++k;
             };
@@ -1044,7 +1083,9 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             using I3 = IntC<3>;
             using Load = IntC<1>;
             using NoLoad = IntC<0>;
-            while (k + (TRIAL ? 4 : 5) <= nb) { step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load()); }
+            for (; k + (TRIAL ? 4 : 5) <= nb; group += 4 * Records::kRow) {
+                step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load());
+            }
             // the grid-map loads follow the last record load (global loads
             // complete in order)
             __builtin_amdgcn_sched_barrier(0);
@@ -1062,9 +1103,7 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) g[s][0] = g[s][1] = g[s][2] = 0.f;
     } else {
-        // each wave adds into its own range of copies; with several waves per
-        // individual, wave w takes the w-th of WAVES consecutive runs of
-        // ceil(n_batches / WAVES) batches (the last runs may be short or empty)
+        // each wave adds into its own range of copies
         const int nslot = L.n_copies * L.stride;
         float4* const accw = sm.u.acc + (WAVES == 1 ? 0 : L.wv * nslot);
         // cleared by whole waves of slots (the array holds a multiple of 64;
@@ -1073,11 +1112,6 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         static_assert(Smem<SLOTS, WAVES>::kSlots % kWave == 0, "clearing stays inside the accumulators");
         for (int k = 0; k < nslot; k += kWave) accw[k + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
         lds_sync<WAVES>();
-        const int nb_all = L.n_batches;
-        const int run = (nb_all + WAVES - 1) / WAVES;
-        const int b0 = WAVES == 1 ? 0 : min(L.wv * run, nb_all);
-        const int nb = WAVES == 1 ? nb_all : min(nb_all - b0, run);
-        const u32x4* const plist_at = L.plist + b0 * kWave;
         const int pmask = L.pmask;
         // an atom's position sits at its slot's byte offset masked to one stride
         auto pos_i = [&](uint32_t w) { return *slot(sm.dyn, w & pmask); };
@@ -1090,24 +1124,10 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
         // unrolled by four with register sets indexed by the batch number
         // mod 4 and mod 2: no loaded value is copied between steps. Slot
         // updates stay in batch order (LDS executes a wave's accesses in
-        // order: batch k's stores precede batch k + 1's loads). Prefetch
-        // indices are clamped to the last batch, so loads need no guard.
+        // order: batch k's stores precede batch k + 1's loads).
         if (nb > 0) {
-            // records through a buffer resource over this wave's batches: the
-            // row offset is a scalar and the lane offset a loop-invariant
-            // register, so a record load costs no vector address arithmetic
-            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<u32x4*>(plist_at), 0, nb * kWave * (int)sizeof(u32x4), kBufferWord3);
-            const int lane_off = lane * (int)sizeof(u32x4);
-            auto record = [&](int b) -> u32x4 {
-                return __builtin_amdgcn_raw_buffer_load_b128(
-                    prsrc, lane_off, uniform(min(b, nb - 1)) * kWave * (int)sizeof(u32x4), 0);
-            };
-            u32x4 R[4];
             float4 Pi[2], Pj[2], Ai[2], Aj[2];
             PairForce F[2];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) R[q] = record(q);
             // the prologue issues its LDS reads in the loop's order (positions
             // of the next batch before the slots of this one), so that at the
             // loop head the slot reads may still be in flight
@@ -1119,13 +1139,14 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             Ai[0] = *slot(accw, F[0].si);
             Aj[0] = *slot(accw, F[0].sj);
             int k = 0;
+            int group = 4 * Records::kRow;
             auto step = [&](auto residue, auto load) {
                 constexpr int r = decltype(residue)::value;  // k mod 4
                 constexpr int c = r & 1, n = (r + 1) & 1;
                 const u32x4 rf = R[(r + 2) & 3];
                 Pi[c] = pos_i(rf.x);
                 Pj[c] = pos_j(rf.x);
-                if constexpr (decltype(load)::value != 0) R[r] = record(k + 4);
+                if constexpr (decltype(load)::value != 0) R[r] = records.load(group, r);
                 __builtin_amdgcn_sched_barrier(0);   // keep the loads at the step's start
                 F[n] = pair_force(R[(r + 1) & 3], Pi[n], Pj[n], r == 1 && decltype(load)::value == 0);
                 store_force(accw, F[c], Ai[c], Aj[c]);
@@ -1141,7 +1162,9 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
             using I3 = IntC<3>;
             using Load = IntC<1>;
             using NoLoad = IntC<0>;
-            while (k + 4 < nb) { step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load()); }
+            for (; k + 4 < nb; group += 4 * Records::kRow) {
+                step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load());
+            }
             // Every record the remaining steps need is loaded. The grid-map
             // loads go here, after the last record load: global loads
             // complete in order, so a record load issued after them would
@@ -1922,6 +1945,7 @@ __device__ void load_ligand2(const uint8_t* __restrict__ blob, Smem2T<FORCES>& s
     L.cls[0] = ii.x;
     L.frag[0] = ok ? ii.y : 0;
     L.orig[0] = ii.z;
+    L.chain[0] = chain_word(blob, L.frag[0]);
     // the prefix sums' positions are lanes of this half
     L.torsion = torsion_word(blob, L.T, a - kFirstTorsion) + (uint32_t)(lane & kHalf) * 0x01010000u;
     const Torsion* tr = reinterpret_cast<const Torsion*>(blob + h->off_tors);
@@ -1951,6 +1975,12 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     const int h = lane >> 5;
     const int hb = h * kHalf;
     const int N = L.N;
+    const int ns = 2 * L.n_batches;              // steps of the pair terms, the first four's records loaded here
+    using Records = PairRecords<kHalf>;
+    const Records records(L.plist, ns, j);
+    u32x4 R[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) R[q] = records.load(0, q);
     float body, rest;                            // the rigid-body genes lie in the half's first row
     half_rows(gene, body, rest);
     const float tx = row_lane<0>(body), ty = row_lane<1>(body), tz = row_lane<2>(body);
@@ -1964,25 +1994,10 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     wave_sync();
     // atom positions relative to the rotation centre, as in `evaluate`
     const float tv[3] = {tx, ty, tz};
-    const int n_duos = (L.max_depth + 1) >> 1;
     float x[3];
     {
         float y0 = L.y0[0][0], y1 = L.y0[0][1], y2 = L.y0[0][2];
-        const uint32_t* row = sm.chain[L.frag[0]];
-        const char* tkh = reinterpret_cast<const char*>(sm.u[h].transforms());
-        for (int d = 0; d < n_duos; ++d) {
-            const uint32_t w = row[d >> 1] >> (16 * (d & 1));
-            float4 T[2][3];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const unsigned k = (w >> (8 * q)) & 255u;
-                const float4* t = reinterpret_cast<const float4*>(
-                    __builtin_assume_aligned(tkh + __umul24(k, 48u), 16));
-                T[q][0] = t[0]; T[q][1] = t[1]; T[q][2] = t[2];
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) apply_transform(T[q], y0, y1, y2);
-        }
+        apply_chain<2>(L.chain[0], sm.chain[L.frag[0]], sm.u[h].transforms(), L.max_depth, y0, y1, y2);
         rotate(Rq, y0, y1, y2, x);
         sm.dyn[h][j] = make_float4(x[0], x[1], x[2], kSqrtElec * L.chg[0][1]);
     }
@@ -2007,23 +2022,12 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     // step s reads the positions of step s + 1 before computing its own pair
     // and loads the record of step s + 4 (register sets indexed by s mod 4
     // and mod 2, steps unrolled by four, no loaded value copied between
-    // steps); prefetch indices are clamped to the last step.
-    const int ns = 2 * L.n_batches;
+    // steps).
     if (ns > 0) {
-        const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<u32x4*>(L.plist), 0, ns * kHalf * (int)sizeof(u32x4), kBufferWord3);
-        const int lane_off = j * (int)sizeof(u32x4);
-        auto record = [&](int s) -> u32x4 {
-            return __builtin_amdgcn_raw_buffer_load_b128(
-                prsrc, lane_off, uniform(min(s, ns - 1)) * kHalf * (int)sizeof(u32x4), 0);
-        };
-        u32x4 R[4];
         float4 Pi[2], Pj[2];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) R[q] = record(q);
         Pi[0] = pos_i(R[0].x);
         Pj[0] = pos_j(R[0].x);
-        int s = 0;
+        int s = 0, group = 4 * Records::kRow;        // group: the rows of steps s + 4 to s + 7, s mod 4 = 0
         auto step = [&](auto residue, auto load) {
             constexpr int r = decltype(residue)::value;  // s mod 4
             constexpr int c = r & 1, n = (r + 1) & 1;
@@ -2038,7 +2042,7 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
                 store_force(acch, F, ai, aj);
             }
             e_lane += F.e;
-            if constexpr (decltype(load)::value != 0) R[r] = record(s + 4);
+            if constexpr (decltype(load)::value != 0) R[r] = records.load(group, r);
             __builtin_amdgcn_sched_barrier(0);
             ++s;
         };
@@ -2048,7 +2052,9 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
         using I3 = IntC<3>;
         using Load = IntC<1>;
         using NoLoad = IntC<0>;
-        while (s + 4 <= ns) { step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load()); }
+        for (; s + 4 <= ns; group += 4 * Records::kRow) {
+            step(I0(), Load()); step(I1(), Load()); step(I2(), Load()); step(I3(), Load());
+        }
         __builtin_amdgcn_sched_barrier(0);
         grid_load<ANY_LAYOUT>(G, L.cls[0], x, tv, tap);
         __builtin_amdgcn_sched_barrier(0);
