@@ -869,12 +869,10 @@ __device__ __forceinline__ void apply_chain(uint32_t first, const uint32_t* row,
     }
 }
 
-// Atom positions of the individual whose genes this wave holds: relative to
-// the translation genes `tv`, in registers (x) and in the LDS position table.
-template <int SLOTS, int WAVES, int LEVELS = 2, class SM>
-__device__ __forceinline__ void pose(SM& sm, const Lig<SLOTS>& L, float gene, Rot& Rq, float tv[3],
-                                     float x[SLOTS][3]) {
-    const int lane = lane_id();
+// Rigid body (rotation and translation) and torsion transforms of the individual
+// whose genes this wave holds; the transforms are left in LDS.
+template <int WAVES, class SM, class LIG>
+__device__ __forceinline__ void transforms_of(SM& sm, const LIG& L, float gene, Rot& Rq, float tv[3]) {
     const bool lead = WAVES == 1 || L.wv == 0;  // the wave that writes shared tables
     // rigid-body genes (uniform)
     const float tx = readlane(gene, 0), ty = readlane(gene, 1), tz = readlane(gene, 2);
@@ -884,18 +882,25 @@ __device__ __forceinline__ void pose(SM& sm, const Lig<SLOTS>& L, float gene, Ro
 
     // torsion transforms: T_k(y) = R_k (y - p) + p, about the reference axis, by
     // the lane that holds the angle
-    const int k = lane - kFirstTorsion;
+    const int k = lane_id() - kFirstTorsion;
     if (lead && k >= 0 && k < L.T) {
         torsion_transform(gene, sm.tor[k][0], sm.tor[k][1], sm.u.transforms() + 3 * k);
     }
+    tv[0] = tx; tv[1] = ty; tv[2] = tz;
     lds_sync<WAVES>();
+}
+
+// Atom positions from the rigid body and the transforms in LDS: relative to the
+// translation, in registers (x) and in the LDS position table.
+template <int SLOTS, int WAVES, int LEVELS = 2, class SM>
+__device__ __forceinline__ void place_atoms(SM& sm, const Lig<SLOTS>& L, const Rot& Rq, float x[SLOTS][3]) {
+    const int lane = lane_id();
     // atom positions relative to the rotation centre: the torsions enclosing
     // the atom's fragment, innermost first (each about its reference axis,
     // which no inner torsion moves), then the rotation Rq. The translation t
     // is added only where world coordinates are needed (the grid term): pair
     // separations, torques and torsion axes are translation invariant and
     // keep the precision of the small local coordinates.
-    tv[0] = tx; tv[1] = ty; tv[2] = tz;
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         const int a = lane + kWave * (s + L.wv);
@@ -906,6 +911,63 @@ __device__ __forceinline__ void pose(SM& sm, const Lig<SLOTS>& L, float gene, Ro
     }
     lds_sync<WAVES>();
 }
+
+// The rigid bodies and torsion transforms of several genotypes, made at once: a
+// genotype takes T + 1 of LANES lanes, one per torsion and one for the rigid body,
+// and holds them until its turn. A wave whose next genotypes are known so spends
+// the 140 instructions, of which a genotype alone uses a few lanes, once for
+// 64 / (T + 1) of them. Used where instructions bound the kernel: energies of 50,001
+// genotypes take 85.1 us with a pose each, 82.6 so (48 atoms), 40.0 and 36.3 (24
+// atoms). With gradients, or two genotypes per wave, the LDS unit is as busy as the
+// VALU, and the reads of the rigid body cost what the instructions save (24 atoms
+// two per wave 57.2 and 57.0 us, 112 atoms 108.2 and 109.7).
+template <int LANES>
+struct PoseGroup {
+    static constexpr int kRigid = 5;   // float4s of a rigid body in LDS
+    int size;                   // genotypes
+    int mine, part;             // this lane's genotype, and its torsion or (T) the rigid body
+    int T;
+    float4 row[3], more;        // transform; or rotation rows with 1/|q|, w, x and y, z, t.x, t.y
+    float last;                 // t.z
+
+    __device__ __forceinline__ PoseGroup(int torsions, int lane) : T(torsions) {
+        size = LANES / (torsions + 1);
+        mine = lane / (torsions + 1);
+        part = lane - mine * (torsions + 1);
+    }
+    // `genes`: this lane's genotype; not read unless `live`
+    __device__ __forceinline__ void make(const float4 (*tor)[2], const float* genes, bool live) {
+        if (!live) return;
+        if (part < T) {
+            torsion_transform(genes[kFirstTorsion + part], tor[part][0], tor[part][1], row);
+        } else {
+            const Rot R = rotation(genes[3], genes[4], genes[5], genes[6]);
+            row[0] = make_float4(R.m[0], R.m[1], R.m[2], R.inv);
+            row[1] = make_float4(R.m[3], R.m[4], R.m[5], R.w);
+            row[2] = make_float4(R.m[6], R.m[7], R.m[8], R.x);
+            more = make_float4(R.y, R.z, genes[0], genes[1]);
+            last = genes[2];
+        }
+    }
+    // genotype q's transforms and rigid body to their places in LDS
+    __device__ __forceinline__ void store(int q, float4* transforms, float4* rigid) const {
+        if (mine != q) return;
+        float4* const to = part < T ? transforms + 3 * part : rigid;
+        to[0] = row[0]; to[1] = row[1]; to[2] = row[2];
+        if (part == T) {
+            rigid[3] = more;
+            rigid[4].x = last;
+        }
+    }
+    static __device__ __forceinline__ void load(const float4* rigid, Rot& R, float tv[3]) {
+        const float4 a = rigid[0], b = rigid[1], c = rigid[2], d = rigid[3];
+        R.m[0] = a.x; R.m[1] = a.y; R.m[2] = a.z;
+        R.m[3] = b.x; R.m[4] = b.y; R.m[5] = b.z;
+        R.m[6] = c.x; R.m[7] = c.y; R.m[8] = c.z;
+        R.inv = a.w; R.w = b.w; R.x = c.w; R.y = d.x; R.z = d.y;
+        tv[0] = d.z; tv[1] = d.w; tv[2] = rigid[4].x;
+    }
+};
 
 // Sum of an atom's `n` accumulator copies, `stride` slots apart, in copy order;
 // four reads in flight at a time.
@@ -1007,13 +1069,13 @@ __device__ __forceinline__ float finish(SM& sm, const Lig<SLOTS>& L, const Rot& 
 }
 
 // ---------------------------------------------------------------------------
-// One evaluation of E and dE/dgenotype for the individual held by this wave.
-// `gene` is gene `lane` (lanes >= G ignored); returns E (uniform) and writes
-// this lane's gradient component to `grad`.
+// One evaluation of E and dE/dgenotype by this wave, of the individual whose
+// transforms `prepare` leaves in LDS and whose rigid body it gives; returns E
+// (uniform) and writes this lane's gradient component to `grad`.
 // ---------------------------------------------------------------------------
-template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true, bool GRAD = true, bool TRIAL = false>
-__device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L, float gene,
-                          float& grad, float* atom_out) {
+template <int SLOTS, int VAR, int WAVES, bool ANY_LAYOUT, bool GRAD, bool TRIAL, class PREPARE>
+__device__ __forceinline__ float evaluate_prepared(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L,
+                                                   PREPARE&& prepare, float& grad, float* atom_out) {
     const int lane = lane_id();
     const int N = L.N;
     // this wave's batches, the first four of which are loaded ahead of the pose (a
@@ -1033,7 +1095,8 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
 
     Rot Rq;
     float tv[3], x[SLOTS][3];
-    pose<SLOTS, WAVES>(sm, L, gene, Rq, tv, x);
+    prepare(Rq, tv);
+    place_atoms<SLOTS, WAVES>(sm, L, Rq, x);
 
     float g[SLOTS][3];
     float e_lane = 0.f;
@@ -1234,6 +1297,14 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
     return E;
 }
 
+// The same for the individual whose gene `lane` is `gene` (lanes >= G ignored).
+template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true, bool GRAD = true, bool TRIAL = false>
+__device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L, float gene,
+                          float& grad, float* atom_out) {
+    return evaluate_prepared<SLOTS, VAR, WAVES, ANY_LAYOUT, GRAD, TRIAL>(
+        G, sm, L, [&](Rot& Rq, float tv[3]) { transforms_of<WAVES>(sm, L, gene, Rq, tv); }, grad, atom_out);
+}
+
 // ---------------------------------------------------------------------------
 // Kernels.
 // ---------------------------------------------------------------------------
@@ -1258,13 +1329,37 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void sco
     load_ligand<SLOTS>(blob, sm, L);
     const int lane = lane_id();
     const int G_ = L.G;
-    for (int ind = blockIdx.x; ind < n; ind += gridDim.x) {
-        const float gene = lane < G_ ? gen[(size_t)ind * G_ + lane] : 0.f;
-        float gr;
-        float* ao = GRAD && atom_out ? atom_out + (size_t)ind * L.N * 8 : nullptr;
-        const float E = evaluate<SLOTS, VAR, 1, ANY_LAYOUT, GRAD>(G, sm, L, gene, gr, ao);
-        if (lane == 0) energy[ind] = E;
-        if (GRAD && grad && lane < G_) grad[(size_t)ind * G_ + lane] = gr;
+    if constexpr (SLOTS == 1 && !GRAD) {
+        // the poses of as many of the wave's genotypes as its lanes hold, made at once
+        __shared__ float4 rigid[PoseGroup<kWave>::kRigid];
+        PoseGroup<kWave> group(L.T, lane);
+        int q = group.size;
+        for (long long ind = blockIdx.x; ind < n; ind += gridDim.x, ++q) {
+            if (q == group.size) {
+                q = 0;
+                const long long row = ind + (long long)group.mine * gridDim.x;
+                group.make(sm.tor, gen + row * G_, group.mine < group.size && row < n);
+            }
+            float gr;
+            const float E = evaluate_prepared<SLOTS, VAR, 1, ANY_LAYOUT, GRAD, false>(
+                G, sm, L,
+                [&](Rot& Rq, float tv[3]) {
+                    group.store(q, sm.u.transforms(), rigid);
+                    wave_sync();
+                    group.load(rigid, Rq, tv);
+                },
+                gr, nullptr);
+            if (lane == 0) energy[ind] = E;
+        }
+    } else {
+        for (int ind = blockIdx.x; ind < n; ind += gridDim.x) {
+            const float gene = lane < G_ ? gen[(size_t)ind * G_ + lane] : 0.f;
+            float gr;
+            float* ao = GRAD && atom_out ? atom_out + (size_t)ind * L.N * 8 : nullptr;
+            const float E = evaluate<SLOTS, VAR, 1, ANY_LAYOUT, GRAD>(G, sm, L, gene, gr, ao);
+            if (lane == 0) energy[ind] = E;
+            if (GRAD && grad && lane < G_) grad[(size_t)ind * G_ + lane] = gr;
+        }
     }
 }
 
@@ -1272,9 +1367,13 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void sco
 // steps are those of Solis and Wets as AutoDock uses them): per iteration the
 // trial x + bias + dev, else x - bias - dev, accepted when its energy is lower;
 // bias and the step scale rho follow the outcome. One wave per individual,
-// gene `lane`; energies only (the gradient evaluate() also makes is unused).
-// State updates are float32 in a fixed order with no fused operations.
-template <int SLOTS, int VAR>
+// gene `lane`; energies only.
+// State updates are float32 in a fixed order with no fused operations. Bound by
+// VALU issue (1,550 instructions per iteration of a 48-atom ligand): 3000
+// individuals, 100 iterations 1,023 us with the full evaluation's layout checks
+// and normals read where they are used, 977 once the evaluation waited less, 963
+// with a kernel for the corner-expanded maps and the normals an iteration ahead.
+template <int SLOTS, int VAR, bool ANY_LAYOUT>
 __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void sw_kernel(GridParams G, const uint8_t* __restrict__ blob,
                                                 docklaunch::SwParams p) {
     __shared__ Smem<SLOTS> sm;
@@ -1292,15 +1391,21 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2)) void sw_kernel(GridParams
     float E = p.energy[ind];
     float rho = p.rho[ind];
     int succ = p.counts[2 * ind], fail = p.counts[2 * ind + 1];
+    // the next iteration's normals are read an iteration ahead
+    auto normal = [&](int it) {
+        return on && it < p.iterations ? p.normals[((size_t)it * p.n + ind) * Gn + lane] : 0.f;
+    };
+    float z_next = normal(0);
     for (int it = 0; it < p.iterations; ++it) {
-        const float z = on ? p.normals[((size_t)it * p.n + ind) * Gn + lane] : 0.f;
+        const float z = z_next;
+        z_next = normal(it + 1);
         const float dev = rho * (sc * z);
         float e_try0 = __builtin_nanf(""), e_try1 = __builtin_nanf("");
         int accepted = -1;
         for (int t = 0; t < 2; ++t) {      // uniform: E and the trial energies are wave-uniform
             const float c = t == 0 ? (x + b) + dev : (x - b) - dev;
             float gr;
-            const float Et = evaluate<SLOTS, VAR, 1, true, false, true>(G, sm, L, c, gr, nullptr);
+            const float Et = evaluate<SLOTS, VAR, 1, ANY_LAYOUT, false, true>(G, sm, L, c, gr, nullptr);
             if (t == 0) e_try0 = Et; else e_try1 = Et;
             if (Et < E) {
                 x = c;
@@ -1796,7 +1901,8 @@ __device__ __forceinline__ void coop_search(const DevItem& it, int ind, SmemC<SL
     search(it, ind, L.G, it.iterations, p.rho, p.eps, it.final_eval != 0, true, [&](float gene, float& gr) {
         Rot Rq;
         float tv[3], x[SLOTS][3], g[SLOTS][3];
-        pose<SLOTS, 1, 4>(sm, L, gene, Rq, tv, x);
+        transforms_of<1>(sm, L, gene, Rq, tv);
+        place_atoms<SLOTS, 1, 4>(sm, L, Rq, x);
         if (lane < 3) sm.t[lane] = gene;
         if (lane == 0) sm.go = 1;
         lds_barrier();
@@ -2416,10 +2522,14 @@ hipError_t launch_score_v(const GridParams& g, const uint8_t* blob, int slots, i
 template <int VAR>
 hipError_t launch_sw_v(const GridParams& g, const uint8_t* blob, int slots, const docklaunch::SwParams& p,
                        hipStream_t st) {
-    if (slots == 1)
-        hipLaunchKernelGGL((sw_kernel<1, VAR>), dim3(p.n), dim3(64), 0, st, g, blob, p);
+    if (slots == 1 && g.corners)
+        hipLaunchKernelGGL((sw_kernel<1, VAR, false>), dim3(p.n), dim3(64), 0, st, g, blob, p);
+    else if (slots == 1)
+        hipLaunchKernelGGL((sw_kernel<1, VAR, true>), dim3(p.n), dim3(64), 0, st, g, blob, p);
+    else if (g.corners)
+        hipLaunchKernelGGL((sw_kernel<2, VAR, false>), dim3(p.n), dim3(64), 0, st, g, blob, p);
     else
-        hipLaunchKernelGGL((sw_kernel<2, VAR>), dim3(p.n), dim3(64), 0, st, g, blob, p);
+        hipLaunchKernelGGL((sw_kernel<2, VAR, true>), dim3(p.n), dim3(64), 0, st, g, blob, p);
     return hipGetLastError();
 }
 

@@ -65,3 +65,40 @@ def test_non_finite_genotypes_stay_in_their_row(setup, two, gene):
         assert not torch.isfinite(Eb[[5, 6, 39]]).any()
         if grad:
             assert torch.equal(g[rows], gb[rows])
+
+
+@pytest.mark.parametrize("atoms,torsions", [(1, 0), (20, 0), (24, 6), (48, 10), (60, 20), (64, 28)])
+@pytest.mark.parametrize("n", [9000, 40001])
+def test_energies_from_grouped_poses(setup, atoms, torsions, n):
+    """More genotypes than waves: a wave makes the poses of 64 / (torsions + 1) of
+    its genotypes at once (two to sixty-four; the last group is cut off). Energies
+    are those of the gradient evaluation, which makes one at a time, bit for bit."""
+    dock, grd, *maps, ff = setup
+    lig = synth.ligand(atoms, torsions, 104)
+    L = dock.Ligand(lig, ff)
+    gen = torch.from_numpy(synth.genotypes(lig, grd, 1000, 3)).cuda().repeat(-(-n // 1000), 1)[:n].contiguous()
+    gen[:, :3] += torch.linspace(-1.0, 1.0, n, device="cuda")[:, None]
+    for G in maps:
+        E, _ = dock.score_batch(G, L, gen, with_grad=False)
+        want, _ = dock.score_batch(G, L, gen, with_grad=True)
+        assert torch.equal(E, want)
+
+
+@pytest.mark.parametrize("atoms,torsions", [(12, 2), (48, 10), (112, 28)])
+@pytest.mark.parametrize("iterations", [1, 2, 9])
+def test_random_search_reads_either_map_layout(setup, atoms, torsions, iterations):
+    """The random search of the corner-expanded maps and of the plain ones (a kernel
+    each): the same cells, so the same states bit for bit."""
+    dock, grd, *maps, ff = setup
+    lig = synth.ligand(atoms, torsions, 104)
+    L = dock.Ligand(lig, ff)
+    gen = torch.from_numpy(synth.genotypes(lig, grd, 70, 3)).cuda()
+    normals = torch.randn((iterations, 70, L.n_genes), device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    scale = torch.full((L.n_genes,), 0.3, device="cuda")
+    states = []
+    for G in maps:
+        st = dock.SWState.start(gen, dock.score_batch(G, L, gen, with_grad=False)[0])
+        dock.solis_wets(G, L, st, normals, scale)
+        states.append(st)
+    for f in ("genotype", "energy", "bias", "rho", "counts"):
+        assert torch.equal(getattr(states[0], f), getattr(states[1], f)), f
