@@ -389,17 +389,22 @@ int shared_wave_blocks(const LsPart& pt, int grid) {
 // (same results), or 0 for a wave per individual. Sharing an individual costs
 // total work (the slot sums, 80 instructions more per wave) and pays while SIMDs
 // would idle: up to the individuals whose blocks are resident at once, 256 with
-// eight waves (48 atoms, per evaluation: 2.6 us against 4.6) and 512 with four
-// (3.6 against 4.9; 64 atoms 6.4 against 7.3). Past that a second round of
-// blocks costs more than waves of their own (600 individuals in two rounds 7.2
-// us against 5.0). For more than 64 atoms four waves gain nothing at 512 (20.3
-// us either way). A call of several launches side by side fills the GPU better
-// with one wave per individual.
+// eight waves and 512 with four. us per evaluation shared, and a wave each:
+//   256 individuals  1 batch 2.27, 2.35   3 batches (24 atoms) 2.27, 2.48
+//                    14 (48 atoms) 2.58, 4.58   90 (112 atoms) 10.0, 18.6
+//   512 individuals  3 batches 2.76, 2.62   5 (28 atoms) 2.81, 3.27
+//                    14 3.65, 4.87   28 (64 atoms) 6.4, 7.1
+// so four waves take ligands of four batches up, and nothing is shared without a
+// pair (1.87, 1.79). Past 512 a second round of blocks costs more than waves of
+// their own (600 individuals of 48 atoms in two rounds 7.2, 5.0). For more than 64
+// atoms four waves gain nothing at 512 (20.3 either way). A call of several
+// launches side by side fills the GPU better with one wave per individual.
 int coop_waves(const LsPlan& plan, const LsPart& pt, int n_cu) {
     if (plan.n_parts != 1 || !pt.corners) return 0;
     if (pt.mode != docklaunch::kSlots1 && pt.mode != docklaunch::kSlots2) return 0;
+    if (pt.batches == 0) return 0;
     const bool keep = pt.batches <= docklaunch::kCoopKeep;
-    for (int waves = 8; waves >= (pt.mode == docklaunch::kSlots1 ? 4 : 8); waves /= 2)
+    for (int waves = 8; waves >= (pt.mode == docklaunch::kSlots1 && pt.batches >= 4 ? 4 : 8); waves /= 2)
         if (pt.units <= (int64_t)docklaunch::coop_blocks_per_cu(pt.mode, waves, keep) * n_cu) return waves;
     return 0;
 }

@@ -1334,10 +1334,11 @@ __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig
 // be plain or corner-expanded; otherwise the corner-expanded copy is bound.
 // GRAD = false, for calls that ask for neither a gradient nor the per-atom
 // output: the energy-only evaluation, same energies bit for bit. It is bound
-// by VALU issue like the full one but issues 0.6 of its instructions, and at
-// its 114 registers four waves fit a SIMD instead of three: 50,001 genotypes
-// of a 48-atom ligand took 139 us with the gradient made and dropped, 90 us so;
-// 65,536 of a 24-atom one 100 and 52 us, two per wave 65 and 40 us.
+// by VALU issue like the full one but issues 0.6 of its instructions, and within
+// 128 registers four waves fit a SIMD instead of three: 50,001 genotypes
+// of a 48-atom ligand took 139 us with the gradient made and dropped, 90 us so
+// (80 with what came since); 65,536 of a 24-atom one 100 and 52 us, two per wave
+// 65 and 40 us.
 template <int SLOTS, int VAR, bool ANY_LAYOUT, bool GRAD>
 __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void score_kernel(
     GridParams G, const uint8_t* __restrict__ blob, int n, const float* __restrict__ gen, float* __restrict__ energy,
@@ -1651,7 +1652,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3
 // One individual per block, for populations too small to fill the GPU with a
 // wave each: the waves of a block share the pair terms of one individual and
 // give the result of the one-wave evaluation bit for bit. A lone wave needs
-// some 11,000 cycles per evaluation (48 atoms, 886 pairs), 6,400 of them in the
+// some 10,500 cycles per evaluation (48 atoms, 886 pairs), 6,000 of them in the
 // pair batches, whose accumulator slots chain one batch to the next, and the
 // rest of the GPU idles.
 //
@@ -1666,11 +1667,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3
 // More batches than a buffer holds go in chunks through two buffers in turn:
 // while one is summed the other is filled, one barrier per chunk.
 //
-// Bound by the leader's serial part, 3,200 of 5,800 cycles. Per evaluation at
-// 256 individuals, one wave against this: 24 atoms 2.6 and 2.4 us, 48 atoms 4.6
-// and 2.6, 64 atoms (28 batches) 6.9 and 4.2, 112 atoms (90 batches) 19.1 and
-// 10.0; with four waves at 512 individuals 48 atoms 4.9 and 3.6, 64 atoms 7.3
-// and 6.4.
+// Bound by the leader's serial part, 3,200 of 5,800 cycles. us per evaluation at
+// 256 individuals, a wave each against this: 24 atoms 2.48 and 2.27, 48 atoms 4.58
+// and 2.58, 64 atoms (28 batches) 6.75 and 4.15, 112 atoms (90 batches) 18.6 and
+// 10.0; with four waves at 512 individuals 48 atoms 4.87 and 3.65, 64 atoms 7.14
+// and 6.38.
 // ---------------------------------------------------------------------------
 constexpr int kPairRow = dockblob::kGatherRow / 16;   // float4s per batch: 64 pairs and a zero
 constexpr int kCoopRows = docklaunch::kCoopKeep;        // batches a buffer holds
