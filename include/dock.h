@@ -299,6 +299,8 @@ int32_t dock_ls_workspace_bytes(int32_t n_items, int64_t* bytes);
 
 /* Runs opts->iterations steps (or the item's own count) on every individual
  * of every item in one persistent launch; items are scheduled longest first.
+ * A call of one-wave items too few to fill the GPU runs one individual per block
+ * of several waves instead (the same results, bit for bit).
  * Items run in up to five kernel families: ligands of <= 64 atoms (one
  * wave per individual), larger ligands with one wave (two atoms per lane),
  * any ligand with two or four waves per individual (128 or 256 threads: wave
