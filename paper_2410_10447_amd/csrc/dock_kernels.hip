@@ -143,12 +143,15 @@ __device__ __forceinline__ float row_lane(float v) { return dpp<0x150 + C>(v); }
 // Lanes whose source lies outside their row add 0; rows a broadcast masks off
 // keep their value. A DPP operand must have been written at least two
 // instructions before: N independent values are stepped side by side, with
-// waits only where fewer than three are.
+// waits only where fewer than three are. Every block ends with two wait states:
+// the compiler does not see what a block wrote last, and a lane read of it needs
+// one, a DPP instruction of its own two (tests/test_asm_waits_cpu.py).
 #define DPP_STEP(r, how) "v_add_f32_dpp " r ", " r ", " r " " how "\n\t"
 #define DPP_ROW "row_mask:0xf bank_mask:0xf bound_ctrl:1"
 #define DPP_STEP1(how) DPP_STEP("%0", how) "s_nop 1\n\t"
 #define DPP_STEP4(how) DPP_STEP("%0", how) DPP_STEP("%1", how) DPP_STEP("%2", how) DPP_STEP("%3", how)
 #define DPP_STEP6(how) DPP_STEP4(how) DPP_STEP("%4", how) DPP_STEP("%5", how)
+#define DPP_END "s_nop 1"
 #define DPP_ROW_SUM(STEP) \
     STEP("quad_perm:[1,0,3,2] " DPP_ROW) STEP("quad_perm:[2,3,0,1] " DPP_ROW) \
     STEP("row_half_mirror " DPP_ROW) STEP("row_mirror " DPP_ROW)
@@ -166,7 +169,7 @@ __device__ __forceinline__ float wave_sum(float v) {
     return readlane(v, 63);
 }
 __device__ __forceinline__ float4 wave_sum4(float4 v) {
-    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) DPP_WAVE(DPP_STEP4) : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) DPP_WAVE(DPP_STEP4) DPP_END : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
     return make_float4(readlane(v.x, 63), readlane(v.y, 63), readlane(v.z, 63), readlane(v.w, 63));
 }
 
@@ -180,7 +183,7 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // Inclusive prefix sums of six values over the 64 lanes.
 __device__ __forceinline__ void wave_scan6(float v[6]) {
-    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_WAVE(DPP_STEP6)
+    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_WAVE(DPP_STEP6) DPP_END
         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
 }
 
@@ -2025,7 +2028,7 @@ __device__ __forceinline__ float half_sum(float v) {
     return lo + hi;
 }
 __device__ __forceinline__ float4 half_sum4(float4 v) {
-    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    asm("s_nop 1\n\t" DPP_ROW_SUM(DPP_STEP4) DPP_END : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
     float4 w = v;
     asm("s_nop 1\n\t" SWAP_ROWS("%0", "%4") SWAP_ROWS("%1", "%5") SWAP_ROWS("%2", "%6") SWAP_ROWS("%3", "%7") "s_nop 1"
         : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w), "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));
@@ -2034,7 +2037,7 @@ __device__ __forceinline__ float4 half_sum4(float4 v) {
 
 // Inclusive prefix sums of six values within each half.
 __device__ __forceinline__ void half_scan6(float v[6]) {
-    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_HALF(DPP_STEP6)
+    asm("s_nop 1\n\t" DPP_ROW_SCAN(DPP_STEP6) DPP_HALF(DPP_STEP6) DPP_END
         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
 }
 
