@@ -299,6 +299,21 @@ __device__ __forceinline__ float4 sum4(float4 v) {
     else return sum4_mfma_bf16<3>(v);
 }
 
+// A variant known at run time only. The kernels that serve several hold one
+// evaluation that chooses here: with one evaluation per variant side by side
+// the ligand lived in scratch memory (328 bytes a lane), and searches on plain
+// maps, 3000 individuals and 41 evaluations, took 505 us instead of 240 (24
+// atoms), 973 instead of 424 (48) and 4,490 instead of 1,857 (112).
+__device__ __forceinline__ float4 sum4_of(int var, float4 v) {
+    switch (var) {
+        case DOCK_REDUCE_MFMA_F32: return sum4<DOCK_REDUCE_MFMA_F32>(v);
+        case DOCK_REDUCE_MFMA_BF16: return sum4<DOCK_REDUCE_MFMA_BF16>(v);
+        case DOCK_REDUCE_MFMA_F16: return sum4<DOCK_REDUCE_MFMA_F16>(v);
+        case DOCK_REDUCE_MFMA_BF16X3: return sum4<DOCK_REDUCE_MFMA_BF16X3>(v);
+        default: return sum4<DOCK_REDUCE_SHUFFLE>(v);
+    }
+}
+
 // The sum of one value, as the first component of sum4<VAR>.
 template <int VAR>
 __device__ __forceinline__ float sum1(float v) {
@@ -1093,7 +1108,8 @@ __device__ __forceinline__ float finish(SM& sm, const Lig<SLOTS>& L, const Rot& 
 // ---------------------------------------------------------------------------
 template <int SLOTS, int VAR, int WAVES, bool ANY_LAYOUT, bool GRAD, bool TRIAL, class PREPARE>
 __device__ __forceinline__ float evaluate_prepared(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L,
-                                                   PREPARE&& prepare, float& grad, float* atom_out) {
+                                                   PREPARE&& prepare, float& grad, float* atom_out,
+                                                   int var = VAR) {
     const int lane = lane_id();
     const int N = L.N;
     // this wave's batches, the first four of which are loaded ahead of the pose (a
@@ -1302,7 +1318,10 @@ __device__ __forceinline__ float evaluate_prepared(const GridParams& G, Smem<SLO
         return sum1<VAR>(e_lane);
     }
 
-    const float E = finish<SLOTS, WAVES>(sm, L, Rq, x, g, e_lane, [](float4 v) { return sum4<VAR>(v); }, grad);
+    const float E = finish<SLOTS, WAVES>(sm, L, Rq, x, g, e_lane, [var](float4 v) {
+        if constexpr (VAR >= 0) return sum4<VAR>(v);
+        else return sum4_of(var, v);
+    }, grad);
     if (atom_out) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
@@ -1321,9 +1340,9 @@ __device__ __forceinline__ float evaluate_prepared(const GridParams& G, Smem<SLO
 // The same for the individual whose gene `lane` is `gene` (lanes >= G ignored).
 template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true, bool GRAD = true, bool TRIAL = false>
 __device__ float evaluate(const GridParams& G, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L, float gene,
-                          float& grad, float* atom_out) {
+                          float& grad, float* atom_out, int var = VAR) {
     return evaluate_prepared<SLOTS, VAR, WAVES, ANY_LAYOUT, GRAD, TRIAL>(
-        G, sm, L, [&](Rot& Rq, float tv[3]) { transforms_of<WAVES>(sm, L, gene, Rq, tv); }, grad, atom_out);
+        G, sm, L, [&](Rot& Rq, float tv[3]) { transforms_of<WAVES>(sm, L, gene, Rq, tv); }, grad, atom_out, var);
 }
 
 // ---------------------------------------------------------------------------
@@ -1527,27 +1546,8 @@ template <int SLOTS, int VAR, int WAVES = 1, bool ANY_LAYOUT = true>
 __device__ void local_search_one(const DevItem& it, int ind, Smem<SLOTS, WAVES>& sm, const Lig<SLOTS>& L,
                                  int iterations, float rho, float eps, bool final_eval) {
     search(it, ind, L.G, iterations, rho, eps, final_eval, WAVES == 1 || L.wv == 0, [&](float x, float& gr) {
-        return evaluate<SLOTS, VAR, WAVES, ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr);
+        return evaluate<SLOTS, VAR, WAVES, ANY_LAYOUT>(it.grid, sm, L, x, gr, nullptr, VAR >= 0 ? VAR : it.variant);
     });
-}
-
-template <int SLOTS, int WAVES>
-__device__ void ls_dispatch(int var_uniform, const DevItem& it, int ind, Smem<SLOTS, WAVES>& sm,
-                            const Lig<SLOTS>& L, const LsParams& p) {
-    const int var = var_uniform >= 0 ? var_uniform : it.variant;
-    const bool fin = it.final_eval != 0;
-    switch (var) {
-        case DOCK_REDUCE_MFMA_F32:
-            local_search_one<SLOTS, DOCK_REDUCE_MFMA_F32, WAVES>(it, ind, sm, L, it.iterations, p.rho, p.eps, fin); break;
-        case DOCK_REDUCE_MFMA_BF16:
-            local_search_one<SLOTS, DOCK_REDUCE_MFMA_BF16, WAVES>(it, ind, sm, L, it.iterations, p.rho, p.eps, fin); break;
-        case DOCK_REDUCE_MFMA_F16:
-            local_search_one<SLOTS, DOCK_REDUCE_MFMA_F16, WAVES>(it, ind, sm, L, it.iterations, p.rho, p.eps, fin); break;
-        case DOCK_REDUCE_MFMA_BF16X3:
-            local_search_one<SLOTS, DOCK_REDUCE_MFMA_BF16X3, WAVES>(it, ind, sm, L, it.iterations, p.rho, p.eps, fin); break;
-        default:
-            local_search_one<SLOTS, DOCK_REDUCE_SHUFFLE, WAVES>(it, ind, sm, L, it.iterations, p.rho, p.eps, fin); break;
-    }
 }
 
 template <int SLOTS, int VAR, int WAVES = 1>
@@ -1555,10 +1555,7 @@ __device__ void ls_run(const DevItem& it, int ind, Smem<SLOTS, WAVES>& sm, const
                        const LsParams& p) {
     // a kernel specialised for one variant runs only items whose grids have
     // the corner-expanded copy bound; the dispatching kernel takes any
-    if constexpr (VAR >= 0)
-        local_search_one<SLOTS, VAR, WAVES, false>(it, ind, sm, L, it.iterations, p.rho, p.eps, it.final_eval != 0);
-    else
-        ls_dispatch<SLOTS, WAVES>(-1, it, ind, sm, L, p);
+    local_search_one<SLOTS, VAR, WAVES, (VAR < 0)>(it, ind, sm, L, it.iterations, p.rho, p.eps, it.final_eval != 0);
 }
 
 // The item of work unit u: the last item with unit_begin <= u (items are
@@ -1943,15 +1940,7 @@ __device__ __forceinline__ void coop_search(const DevItem& it, int ind, SmemC<SL
             e_lane += ok ? e.x : 0.f;
         }
         const int var = it.variant;
-        return finish<SLOTS, 1>(sm, L, Rq, x, g, e_lane, [var](float4 v) {
-            switch (var) {
-                case DOCK_REDUCE_MFMA_F32: return sum4<DOCK_REDUCE_MFMA_F32>(v);
-                case DOCK_REDUCE_MFMA_BF16: return sum4<DOCK_REDUCE_MFMA_BF16>(v);
-                case DOCK_REDUCE_MFMA_F16: return sum4<DOCK_REDUCE_MFMA_F16>(v);
-                case DOCK_REDUCE_MFMA_BF16X3: return sum4<DOCK_REDUCE_MFMA_BF16X3>(v);
-                default: return sum4<DOCK_REDUCE_SHUFFLE>(v);
-            }
-        }, gr);
+        return finish<SLOTS, 1>(sm, L, Rq, x, g, e_lane, [var](float4 v) { return sum4_of(var, v); }, gr);
     });
     if (lane == 0) sm.go = 0;
     lds_barrier();
