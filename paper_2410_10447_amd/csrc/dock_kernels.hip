@@ -404,7 +404,7 @@ __device__ __forceinline__ uint32_t chain_word(const uint8_t* blob, int frag) {
 }
 
 // Header fields and this wave's atoms (`wv`: which 64 x SLOTS of them).
-template <int SLOTS>
+template <int SLOTS, bool FOLLOW = true>
 __device__ __forceinline__ void load_atoms(const uint8_t* __restrict__ blob, int wv, Lig<SLOTS>& L) {
     const Header* h = reinterpret_cast<const Header*>(blob);
     const int lane = lane_id();
@@ -433,11 +433,15 @@ __device__ __forceinline__ void load_atoms(const uint8_t* __restrict__ blob, int
         // lanes past the last atom follow atom 0 without its charge: they read
         // the map cells that it reads (at a place of their own, on plain maps,
         // a random search over 24 atoms took 155 us instead of 150), and no
-        // torsion moves the root (unused pair lanes may read their positions)
-        L.y0[s][0] = r.x; L.y0[s][1] = r.y; L.y0[s][2] = r.z;
+        // torsion moves the root (unused pair lanes may read their positions).
+        // Without FOLLOW they sit at the rotation centre: the shared evaluation,
+        // on corner-expanded maps only, is faster so (500 individuals of 64 atoms
+        // 6.5 us per evaluation, else 6.9; 150 of 48 2.30 and 2.32)
+        const bool real = FOLLOW || ok;
+        L.y0[s][0] = real ? r.x : 0.f; L.y0[s][1] = real ? r.y : 0.f; L.y0[s][2] = real ? r.z : 0.f;
         L.chg[s][0] = ok ? c.x : 0.f; L.chg[s][1] = ok ? c.y : 0.f; L.chg[s][2] = ok ? c.z : 0.f;
         L.cls[s] = ii.x;
-        L.frag[s] = ii.y;
+        L.frag[s] = real ? ii.y : 0;
         L.orig[s] = ii.z;
         L.chain[s] = chain_word(blob, L.frag[s]);
     }
@@ -1887,7 +1891,7 @@ __device__ __forceinline__ void coop_search(const DevItem& it, int ind, SmemC<SL
     // the leaders of the blocks that share a CU sit on different SIMDs
     const int role = uniform((wave + ((int)blockIdx.x >> 8)) & (W - 1));
     Lig<SLOTS> L;
-    load_atoms<SLOTS>(it.blob, 0, L);
+    load_atoms<SLOTS, false>(it.blob, 0, L);
     const Header* h = reinterpret_cast<const Header*>(it.blob);
     CoopPairs c;
     c.table = uniform_ptr(reinterpret_cast<const u32x4*>(it.blob + h->off_gather));
