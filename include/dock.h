@@ -287,8 +287,10 @@ typedef struct {
     float rho;                   /* decay, 0 < rho < 1 (0.8) */
     float eps;                   /* conditioner, > 0 (1e-2) */
     int32_t variant;             /* default DOCK_REDUCE_* */
-    int32_t threads_per_ind;     /* 0 (= 64), 64, 128 or 256: threads (waves of 64)
-                                    per individual; with 128 or 256 the waves split
+    int32_t threads_per_ind;     /* 64, 128 or 256: threads (waves of 64) per
+                                    individual, or 0: 64, but a small call may share
+                                    its individuals (dock_local_search_batch);
+                                    with 128 or 256 the waves split
                                     the pair batches (and, past 64 atoms, the first
                                     two waves the atoms) */
     uint32_t flags;              /* DOCK_LS_FINAL_EVAL | DOCK_LS_SEPARATE_LAUNCHES */
@@ -299,8 +301,11 @@ int32_t dock_ls_workspace_bytes(int32_t n_items, int64_t* bytes);
 
 /* Runs opts->iterations steps (or the item's own count) on every individual
  * of every item in one persistent launch; items are scheduled longest first.
- * A call of one-wave items too few to fill the GPU runs one individual per block
- * of several waves instead (the same results, bit for bit).
+ * A call of one-wave items too few to fill the GPU, with no number of threads
+ * asked for, runs one individual per block of several waves instead (the same
+ * results, bit for bit; dock_ls_shared_waves). That takes more of the GPU and
+ * less time. A call on another stream than the default one may have others
+ * beside it and does so up to a quarter of the individuals only.
  * Items run in up to five kernel families: ligands of <= 64 atoms (one
  * wave per individual), larger ligands with one wave (two atoms per lane),
  * any ligand with two or four waves per individual (128 or 256 threads: wave
@@ -339,6 +344,12 @@ int32_t dock_local_search_batch(const dock_ls_item* items, int32_t n_items,
  * device work, no allocation on the device. */
 int32_t dock_ls_launches(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* opts,
                          int32_t* n_launches);
+
+/* Waves that would share each individual of the call dock_local_search_batch
+ * makes with these arguments on the current device: 4 or 8, or 0 when its items
+ * run as their families do. Validation as above, no device work. */
+int32_t dock_ls_shared_waves(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* opts, void* stream,
+                             int32_t* n_waves);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same

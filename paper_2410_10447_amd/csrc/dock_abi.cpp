@@ -191,6 +191,7 @@ struct LsPlan {
     LsPart part[kLsFamilies];
     int n_parts = 0;
     int64_t table_bytes = 0;
+    bool automatic = true;          // no item with work asks for a number of threads
 };
 
 // Validates a local-search call and builds its device item table (header of
@@ -283,6 +284,7 @@ int32_t ls_plan(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* 
                       ((int64_t)H->n_batches * 90 + (int64_t)d.slots * (150 + 20 * P.max_depth) + 500);
         const int f = two ? 4 : (tpi == 256 ? 0 : (tpi == 128 ? 1 : (d.slots == 1 ? 3 : 2)));
         fam[n_dev] = f;
+        plan.automatic = plan.automatic && it.threads_per_ind == 0 && o->threads_per_ind == 0;
         buf.batches[n_dev] = H->n_batches;
         any_fam[f] = true;
         var_u = (var_u == -2 || var_u == var) ? var : -1;
@@ -393,19 +395,38 @@ int shared_wave_blocks(const LsPart& pt, int grid) {
 //   256 individuals  1 batch 2.27, 2.35   3 batches (24 atoms) 2.27, 2.48
 //                    14 (48 atoms) 2.58, 4.58   90 (112 atoms) 10.0, 18.6
 //   512 individuals  3 batches 2.76, 2.62   5 (28 atoms) 2.81, 3.27
-//                    14 3.65, 4.87   28 (64 atoms) 6.4, 7.1
+//                    14 3.65, 4.87   28 (64 atoms) 6.4, 7.1 (four waves spill 49
+//                    registers at more than 16 batches)
 // so four waves take ligands of four batches up, and nothing is shared without a
 // pair (1.87, 1.79). Past 512 a second round of blocks costs more than waves of
 // their own (600 individuals of 48 atoms in two rounds 7.2, 5.0). For more than 64
 // atoms four waves gain nothing at 512 (20.3 either way). A call of several
 // launches side by side fills the GPU better with one wave per individual.
-int coop_waves(const LsPlan& plan, const LsPart& pt, int n_cu) {
+//
+// Beside other work there are no idle SIMDs to take, and shared blocks (of which
+// a CU holds one or two) queue. us for four searches on four streams, 100 steps,
+// each of
+//                64 individuals          256                     500
+//               shared  a wave each     shared  a wave each     shared  a wave each
+//   24 atoms      231       304            865      341
+//   48            251       526            934      616          1,220      663
+//   64            434       869          1,690      993          2,483    1,039
+//   112           992     2,342          4,003    2,425
+// A call cannot see what runs beside it, but calls that may overlap need streams
+// of their own, and four run at once (the hardware queues of a process). So calls
+// on other streams than the default one share up to a quarter of the individuals,
+// and a call that asks for a number of threads is given it.
+constexpr int kCallsAtOnce = 4;
+
+int coop_waves(const LsPlan& plan, const LsPart& pt, int n_cu, hipStream_t stream) {
+    if (!plan.automatic) return 0;
     if (plan.n_parts != 1 || !pt.corners) return 0;
     if (pt.mode != docklaunch::kSlots1 && pt.mode != docklaunch::kSlots2) return 0;
     if (pt.batches == 0) return 0;
     const bool keep = pt.batches <= docklaunch::kCoopKeep;
     for (int waves = 8; waves >= (pt.mode == docklaunch::kSlots1 && pt.batches >= 4 ? 4 : 8); waves /= 2)
-        if (pt.units <= (int64_t)docklaunch::coop_blocks_per_cu(pt.mode, waves, keep) * n_cu) return waves;
+        if (pt.units * (stream ? kCallsAtOnce : 1) <= (int64_t)docklaunch::coop_blocks_per_cu(pt.mode, waves, keep) * n_cu)
+            return waves;
     return 0;
 }
 
@@ -451,7 +472,7 @@ int32_t ls_launch(const LsPlan& plan, const LsPlanBuf& buf, void* ws, const dock
         p.rho = o->rho;
         p.eps = o->eps;
         hipStream_t s_k = (k == 0 || !side) ? stream : side->stream[k - 1];
-        const int waves = coop_waves(plan, pt, n_cu);
+        const int waves = coop_waves(plan, pt, n_cu, stream);
         launch_err = waves ? docklaunch::launch_ls_coop(p, pt.mode, waves, pt.batches <= docklaunch::kCoopKeep,
                                                         (int)units, s_k)
                            : docklaunch::launch_ls(p, pt.mode, pt.variant, grid, s_k);
@@ -692,6 +713,27 @@ int32_t dock_ls_launches(const dock_ls_item* items, int32_t n_items, const dock_
     const int32_t st = ls_plan(items, n_items, o, buf, plan);
     if (st != DOCK_OK) return st;
     *n_launches = plan.n_parts;
+    return ok();
+}
+
+int32_t dock_ls_shared_waves(const dock_ls_item* items, int32_t n_items, const dock_ls_opts* o, void* stream,
+                             int32_t* n_waves) {
+    if (!n_waves) return fail(DOCK_EINVAL, "dock_ls_shared_waves: NULL n_waves");
+    if (n_items < 0 || (n_items > 0 && !items)) return fail(DOCK_EINVAL, "dock_ls_shared_waves: bad items");
+    std::vector<docklaunch::DevItem> dev(std::max(n_items, 1));
+    std::vector<int64_t> cost(std::max(n_items, 1));
+    std::vector<int> fam(std::max(n_items, 1)), batches(std::max(n_items, 1)), idx(std::max(n_items, 1));
+    std::vector<uint8_t> table(docklaunch::kWorkspaceHeader + (size_t)std::max(n_items, 1) * sizeof(docklaunch::DevItem));
+    LsPlanBuf buf{dev.data(), cost.data(), fam.data(), batches.data(), idx.data(), table.data()};
+    LsPlan plan;
+    int32_t st = ls_plan(items, n_items, o, buf, plan);
+    if (st != DOCK_OK) return st;
+    *n_waves = 0;
+    if (plan.n_parts == 0) return ok();
+    int32_t n_cu = 0;
+    st = device_cu_count(n_cu);
+    if (st != DOCK_OK) return st;
+    *n_waves = coop_waves(plan, plan.part[0], n_cu, (hipStream_t)stream);
     return ok();
 }
 

@@ -53,7 +53,8 @@ ABI_SYMBOLS = (
     "dock_create_ligand", "dock_ligand_info_get", "dock_ligand_export", "dock_ligand_upload",
     "dock_destroy_ligand", "dock_score_batch", "dock_ls_workspace_bytes",
     "dock_select_rows", "dock_gather_rows", "dock_scatter_rows", "dock_ls_start",
-    "dock_local_search_batch", "dock_local_search_batch_static", "dock_ls_launches", "dock_block_sum4",
+    "dock_local_search_batch", "dock_local_search_batch_static", "dock_ls_launches", "dock_ls_shared_waves",
+    "dock_block_sum4",
     "dock_ga_step", "dock_solis_wets_batch",
 )
 
@@ -154,6 +155,7 @@ def lib():
         "dock_local_search_batch": ([C.POINTER(LsItem), i32, C.POINTER(LsOpts), vp, i64, vp], i32),
         "dock_local_search_batch_static": ([C.POINTER(LsItem), i32, C.POINTER(LsOpts), vp], i32),
         "dock_ls_launches": ([C.POINTER(LsItem), i32, C.POINTER(LsOpts), C.POINTER(i32)], i32),
+        "dock_ls_shared_waves": ([C.POINTER(LsItem), i32, C.POINTER(LsOpts), vp, C.POINTER(i32)], i32),
         "dock_block_sum4": ([vp, vp, i32, i32, i32, i32, vp], i32),
         "dock_ga_step": ([C.POINTER(GaStepDesc), vp], i32),
         "dock_select_rows": ([vp, i32, C.c_float, vp, vp, vp], i32),
@@ -538,7 +540,9 @@ def local_search(jobs, iterations: int, rho: float = 0.8, eps: float = 1e-2,
 
     State tensors are updated in place. `workspace` (uint8 CUDA tensor) is
     allocated if not given; `items` may pass a prebuilt item array.
-    `threads_per_ind` (0/64/128/256) is the default for jobs that leave it at 0.
+    `threads_per_ind` (0/64/128/256) is the default for jobs that leave it at 0;
+    left at 0 by both, a small call shares its individuals among the waves of a
+    block (same results; see `ls_shared_waves`), 64 keeps one wave per individual.
     `separate_launches` runs each kernel family in a launch of its own.
     """
     import torch
@@ -570,6 +574,16 @@ def ls_launches(jobs, iterations: int, variant: int = REDUCE_SHUFFLE, final_eval
                flags=(LS_FINAL_EVAL if final_eval else 0) | (LS_SEPARATE_LAUNCHES if separate_launches else 0))
     n = C.c_int32(0)
     _check(lib().dock_ls_launches(items, n_items, C.byref(o), C.byref(n)))
+    return n.value
+
+
+def ls_shared_waves(jobs, iterations: int, variant: int = REDUCE_SHUFFLE, final_eval: bool = True,
+                    threads_per_ind: int = 0, separate_launches: bool = False, stream=None) -> int:
+    """Waves that would share each individual of this local_search call, or 0."""
+    o = LsOpts(iterations=iterations, rho=0.8, eps=1e-2, variant=variant, threads_per_ind=threads_per_ind,
+               flags=(LS_FINAL_EVAL if final_eval else 0) | (LS_SEPARATE_LAUNCHES if separate_launches else 0))
+    n = C.c_int32(0)
+    _check(lib().dock_ls_shared_waves(make_items(jobs), len(jobs), C.byref(o), _stream_handle(stream), C.byref(n)))
     return n.value
 
 

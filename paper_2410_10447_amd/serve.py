@@ -372,6 +372,7 @@ class GpuExecutor:
             pick = autotune.choose(L.n_atoms, L.n_torsions)
             var = int(pick["variant"])
             tpi = int(pick.get("threads_per_ind", 64))
+            tpi = 0 if tpi == 64 else tpi   # one wave's family, left open to sharing in small chunks
             plain = bool(pick.get("plain_maps", False))
             two = bool(pick.get("two_per_wave", False))
         return {"ligand": L, "state": st, "grids": self.grids[spec.grid_id], "host": host,
