@@ -220,6 +220,20 @@ def _need(name, t, shape, dtype, device=None, placement=True):
         raise ValueError(f"{name}: on {t.device}, expected {device}")
 
 
+def _outside_modes() -> bool:
+    """Whether nothing follows tensor operations here: no function transform, mode,
+    forward-mode level, tracing or compilation. False where this torch, whose
+    private names tell, does not have them."""
+    import torch
+    try:
+        return (torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
+                and torch._C._functorch.peek_interpreter_stack() is None
+                and torch.autograd.forward_ad._current_level < 0
+                and torch._C._get_tracing_state() is None and not torch.compiler.is_compiling())
+    except AttributeError:
+        return False
+
+
 def _plain_rows(t) -> bool:
     """Whether `t` is a float32 [n, G] matrix that a kernel on the current device
     may read by its address: an ordinary CUDA tensor outside of autograd, of
@@ -228,11 +242,7 @@ def _plain_rows(t) -> bool:
     return (type(t) is torch.Tensor and t.is_cuda and t.dtype == torch.float32 and t.layout == torch.strided
             and t.dim() == 2 and t.shape[1] > 0 and t.numel() < 2 ** 31 and not t.requires_grad
             and not t.is_conj() and not t.is_neg()
-            and t.device.index == torch.cuda.current_device()
-            and torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
-            and torch._C._functorch.peek_interpreter_stack() is None
-            and torch.autograd.forward_ad._current_level < 0
-            and torch._C._get_tracing_state() is None and not torch.compiler.is_compiling())
+            and t.device.index == torch.cuda.current_device() and _outside_modes())
 
 
 # ---------------------------------------------------------------------------
