@@ -1,8 +1,8 @@
 // HIP kernels of the docking hot path for gfx950 (MI355X, CDNA4, wave64).
 //
-// One wave owns one individual. The per-evaluation pipeline (Sec. 2.1 of the
-// paper: pose from the genotype, pairwise free-energy terms, gradient and
-// torque sums, ADADELTA step) runs entirely inside the wave:
+// One wave owns one individual, but for the layouts below. The per-evaluation
+// pipeline (Sec. 2.1 of the paper: pose from the genotype, pairwise free-energy
+// terms, gradient and torque sums, ADADELTA step) runs entirely inside the wave:
 //
 //   genotype (lane c holds gene c)
 //   -> torsion transforms (lane k: Rodrigues rotation about bond k)
@@ -16,9 +16,12 @@
 //      variants); torque and torsion torques by a wave prefix scan
 //   -> gradient with respect to the genotype, ADADELTA update.
 //
-// No barrier spans more than one wave, no LDS or global float atomics are
-// used, and every sum runs in a fixed order, so results are deterministic
-// run to run and independent of what else shares the launch.
+// Two waves or four may hold an individual (ls_kernel_mw), two individuals a wave
+// (ls_kernel_two, score_kernel_two), and the waves of a block may share the pair
+// terms of one individual (ls_kernel_coop, the same results as a wave each). Only
+// kernels with several waves per individual have block barriers, no LDS or global
+// float atomics are used, and every sum runs in a fixed order, so results are
+// deterministic run to run and independent of what else shares the launch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -29,9 +32,13 @@
 #include "dock_blob.h"
 #include "dock_launch.h"
 
-// No fused operation but those written out (fmaf), so that every kernel that
-// evaluates an individual rounds alike whatever else the compiler finds to
-// share there: searches amplify a last-bit difference within a few steps.
+// No fused operation but those written out (fmaf), so that a kernel's rounding
+// does not hang on what else the compiler finds to share there: searches amplify a
+// last-bit difference within a few steps. The kernels do not all round alike:
+// which square of a separation (pair_term's xfirst) or of an outside distance
+// (grid_term's XFIRST) is added first is what each kernel's results have always
+// been formed with, by batch and by kernel, and is kept for their sake. The trial
+// energies of a random search can so differ from dock_score_batch's in last bits.
 #pragma clang fp contract(off)
 
 namespace {
@@ -951,7 +958,7 @@ __device__ __forceinline__ void place_atoms(SM& sm, const Lig<SLOTS>& L, const R
 }
 
 // The rigid bodies and torsion transforms of several genotypes, made at once: a
-// genotype takes T + 1 of LANES lanes, one per torsion and one for the rigid body,
+// genotype takes T + 1 of the lanes, one per torsion and one for the rigid body,
 // and holds them until its turn. A wave whose next genotypes are known so spends
 // the 140 instructions, of which a genotype alone uses a few lanes, once for
 // 64 / (T + 1) of them. Used where instructions bound the kernel: energies of 50,001
@@ -959,7 +966,6 @@ __device__ __forceinline__ void place_atoms(SM& sm, const Lig<SLOTS>& L, const R
 // atoms). With gradients, or two genotypes per wave, the LDS unit is as busy as the
 // VALU, and the reads of the rigid body cost what the instructions save (24 atoms
 // two per wave 57.2 and 57.0 us, 112 atoms 108.2 and 109.7).
-template <int LANES>
 struct PoseGroup {
     static constexpr int kRigid = 5;   // float4s of a rigid body in LDS
     int size;                   // genotypes
@@ -969,7 +975,7 @@ struct PoseGroup {
     float last;                 // t.z
 
     __device__ __forceinline__ PoseGroup(int torsions, int lane) : T(torsions) {
-        size = LANES / (torsions + 1);
+        size = kWave / (torsions + 1);
         mine = lane / (torsions + 1);
         part = lane - mine * (torsions + 1);
     }
@@ -1377,8 +1383,8 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void sco
     const int G_ = L.G;
     if constexpr (SLOTS == 1 && !GRAD) {
         // the poses of as many of the wave's genotypes as its lanes hold, made at once
-        __shared__ float4 rigid[PoseGroup<kWave>::kRigid];
-        PoseGroup<kWave> group(L.T, lane);
+        __shared__ float4 rigid[PoseGroup::kRigid];
+        PoseGroup group(L.T, lane);
         int q = group.size;
         for (long long ind = blockIdx.x; ind < n; ind += gridDim.x, ++q) {
             if (q == group.size) {
@@ -1888,7 +1894,8 @@ __device__ __forceinline__ void coop_search(const DevItem& it, int ind, SmemC<SL
     constexpr int kBuffers = KEEP ? 1 : 2;
     const int lane = lane_id();
     const int wave = uniform((int)threadIdx.x >> 6);
-    // the leaders of the blocks that share a CU sit on different SIMDs
+    // the leaders of the two blocks that share a CU (of 256) sit on different SIMDs;
+    // on another number of CUs only that placement is lost
     const int role = uniform((wave + ((int)blockIdx.x >> 8)) & (W - 1));
     Lig<SLOTS> L;
     load_atoms<SLOTS, false>(it.blob, 0, L);
@@ -2095,7 +2102,6 @@ __device__ float evaluate2(const GridParams& G, Smem2T<GRAD>& sm, const Lig<1>& 
     const int lane = lane_id();
     const int j = lane & (kHalf - 1);
     const int h = lane >> 5;
-    const int hb = h * kHalf;
     const int N = L.N;
     const int ns = 2 * L.n_batches;              // steps of the pair terms, the first four's records loaded here
     using Records = PairRecords<kHalf>;

@@ -120,7 +120,6 @@ struct SwParams {
 hipError_t launch_sw(const GridParams& g, const uint8_t* blob, int slots, int variant, const SwParams& p,
                      hipStream_t stream);
 
-// One GA generation step (the operators of dock_ga_step).
 // The state of a search before its first step (dock_ls_start).
 struct LsStartParams {
     const float* source;      // [n][n_genes]
@@ -131,6 +130,7 @@ struct LsStartParams {
 };
 hipError_t launch_ls_start(const LsStartParams& p, hipStream_t stream);
 
+// One GA generation step (the operators of dock_ga_step).
 struct GaParams {
     const float* genotypes;   // [n_runs][pop][n_genes]
     const float* energies;    // [n_runs][pop]

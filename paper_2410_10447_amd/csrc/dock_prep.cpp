@@ -474,10 +474,9 @@ std::vector<uint32_t> arrange_batch(const std::vector<uint32_t>& real, const uin
         ++lc.c16[0][best][tail[e]];
         ++lc.c16[1][best][head[e]];
     }
-    // free slots (copy, atom): unused copies of real atoms, then every slot of
-    // the atoms N .. S-1 past the end
-    // past the end, listed per residue: the next one is the first, in that
-    // order, of a residue that the pass uses least
+    // free slots (copy, atom): unused copies of real atoms and every slot of the
+    // atoms N .. S-1 past the end, listed per residue: the next one is the first,
+    // by copy and atom, of a residue that the pass uses least
     struct Slot { int copy, atom, order; };
     Slot free_slots[16][dockblob::kMaxSlots / 16];   // S is a multiple of 16, C * S at most kMaxSlots
     int n_free[16] = {}, next_slot[16] = {};
