@@ -1421,7 +1421,9 @@ __global__ __launch_bounds__(64, (SLOTS == 1 ? 3 : 2) + (GRAD ? 0 : 1)) void sco
 // bias and the step scale rho follow the outcome. One wave per individual,
 // gene `lane`; energies only.
 // State updates are float32 in a fixed order with no fused operations. Bound by
-// VALU issue (1,550 instructions per iteration of a 48-atom ligand): 3000
+// VALU issue (1,540 instructions per iteration of a 48-atom ligand), which fills 80 %
+// of the launch: of the 2.9 waves that each SIMD gets, 2.1 are there on average
+// (trials per individual differ by 6 % at most, so it is not their number): 3000
 // individuals, 100 iterations 1,023 us with the full evaluation's layout checks
 // and normals read where they are used, 977 once the evaluation waited less, 963
 // with a kernel for the corner-expanded maps and the normals an iteration ahead.
@@ -1678,7 +1680,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3
 // More batches than a buffer holds go in chunks through two buffers in turn:
 // while one is summed the other is filled, one barrier per chunk.
 //
-// Bound by the leader's serial part, 3,200 of 5,800 cycles. us per evaluation at
+// Bound by the leader's serial part, 3,500 of 5,800 cycles (150 individuals of 48
+// atoms: pose 1,480, shared part 2,280, copy sums 390, totals and gradient 1,230,
+// step 390), for long pair lists by the shared one (112 atoms, 89 batches: 17,500 of
+// 22,700). Four waves on more than sixteen batches spill 49 registers. us per evaluation at
 // 256 individuals, a wave each against this: 24 atoms 2.48 and 2.27, 48 atoms 4.58
 // and 2.58, 64 atoms (28 batches) 6.75 and 4.15, 112 atoms (90 batches) 18.6 and
 // 10.0; with four waves at 512 individuals 48 atoms 4.87 and 3.65, 64 atoms 7.14
